@@ -17,7 +17,7 @@ LIBDIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(LIBDIR, "liblair.so")
 ARCH = os.environ.get("LAIR_OFFLOAD_ARCH", "gfx950")
 
-HIP_SOURCES = ["k_setup.hip", "k_cycle.hip", "k_batch.hip", "k_krylov.hip", "k_nodal.hip", "k_split.hip", "lair_api.cpp",
+HIP_SOURCES = ["k_setup.hip", "k_cycle.hip", "k_tail.hip", "k_batch.hip", "k_krylov.hip", "k_nodal.hip", "k_split.hip", "lair_api.cpp",
                "setup.cpp", "solve.cpp", "noalloc.cpp",
                "profile.cpp", "alloc.cpp"]
 CXX_SOURCES = ["rs_split.cpp"]

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "lair_internal.hpp"
+#include "tail.hpp"
 
 namespace lair {
 
@@ -68,6 +69,19 @@ struct Level {
     // Jacobi sweeps read, and the sweeps' right-hand side D^{-1} b
     DevArr<double> ndinv, av, bt;
     DevArr<float> av32, bt32;
+};
+
+// The levels from `start` on that one workgroup takes (tail.hpp), packed for
+// one vector type, number of right-hand sides and direction.
+struct Tail {
+    int w = 0;                 // bytes of a vector entry
+    int32_t nrhs = 0;
+    bool transpose = false;
+    size_t start = 0;
+    DevArr<char> blob;
+    std::unique_ptr<TailArgs<double>> a64;
+    std::unique_ptr<TailArgs<float>> a32;
+    double bytes = 0.0, flops = 0.0;   // algorithmic, of its levels
 };
 
 }  // namespace lair
@@ -127,6 +141,8 @@ struct lair_hierarchy {
         for (auto &g : graphs) (void)hipGraphExecDestroy(g.exec);
         graphs.clear();
     }
+    // packed tails, made when a cycle first asks for one (new values: cleared)
+    std::vector<lair::Tail> tails;
     ~lair_hierarchy() {
         drop_graphs();
         if (gstream) (void)hipStreamDestroy(gstream);

@@ -381,6 +381,15 @@ k_resid_norm(int32_t nrows, int T, const int32_t *rp, const int32_t *cj, const d
 // power of two >= the mean row length gives `team`).
 static inline int scalar_team(int team) { return team >= 4 ? team / 4 : 1; }
 
+void cycle_team(int team, int nrhs, int w, bool jacobi, uint8_t *lg, uint8_t *ll) {
+    const int L = nrhs == 1 ? 1 : nrhs / (w == 4 && nrhs >= 4 ? 4 : 2);
+    const int T = nrhs == 1 ? std::min(scalar_team(team), 64)
+                            : jacobi ? vec_team_jacobi(L, team) : vec_team(L, team);
+    *ll = *lg = 0;
+    while ((1 << *ll) < L) ++*ll;
+    while ((L << *lg) < T) ++*lg;
+}
+
 static inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 // SEL: the source is split by point type (x at F columns, xC where

@@ -3939,7 +3939,7 @@ k_dense_gj_inv(int32_t n, const double *dense, double *inv, int32_t *info) {
 bool launch_dense_gj_inv(int32_t n, const double *dense, double *inv, int32_t *info,
                          hipStream_t s);
 
-static size_t max_lds_per_block() {
+size_t max_lds_per_block() {
     static size_t cached = 0;
     if (!cached) {
         int dev = 0, v = 0;

@@ -375,6 +375,8 @@ void launch_to_float(const double *in, float *out, int64_t n, hipStream_t s);
 void launch_block_inverse(int32_t nblk, int32_t k, const int32_t *rp,
                           const int32_t *cj, const double *v, double *dinv,
                           int32_t *bad, hipStream_t s);
+// LDS a workgroup may ask for on this device, in bytes
+size_t max_lds_per_block();
 // dense coarsest factorisation
 void launch_dense_from_csr(int32_t n, const int32_t *rp, const int32_t *cj,
                            const double *v, double *dense, hipStream_t s);
@@ -399,6 +401,10 @@ struct CsrView {
     int32_t team;      // lanes per row for single right-hand sides
     const int32_t *cjt = nullptr;   // columns tagged with the C/F type, or null
 };
+// Lanes per row of the products (or the Jacobi sweeps) of nrhs right-hand
+// sides of w-byte values, for a matrix of single-vector team `team`: 2^lg
+// lanes hold a share of the row each, of 2^ll consecutive entries a step.
+void cycle_team(int team, int nrhs, int w, bool jacobi, uint8_t *lg, uint8_t *ll);
 // cjt[p] = cj[p] with bit 31 set when cf[cj[p]] = 1 (C-point)
 void launch_tag_columns(int64_t nnz, const int32_t *cj, const int8_t *cf, int32_t *cjt,
                         hipStream_t s);

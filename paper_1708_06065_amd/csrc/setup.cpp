@@ -1441,6 +1441,7 @@ void update_diag_impl(lair_hierarchy *h, const double *diag, int32_t on_device,
                 L0.A.cj.get(), L0.A.v.get(), dd);
     LAIR_LAUNCH_CHECK();
     h->drop_graphs();
+    h->tails.clear();
     h->have_transpose = false;
     h->n_singular = 0;
     DevArr<int64_t> tmp;

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "hierarchy.hpp"
+#include "tail.hpp"
 
 namespace lair {
 
@@ -161,6 +162,198 @@ static bool ffc(lair_hierarchy *h, Level &Lv, const VT *b, VT *x, int32_t nrhs,
     return false;
 }
 
+// ---------------------------------------------------------------------------
+// The levels that one workgroup takes (k_tail.hip)
+// ---------------------------------------------------------------------------
+// A level is worth a workgroup while it is small: the workgroup moves its
+// entries through one CU, the launches through the whole chip.  Solves of
+// 2-D, 3-D and DG problems, microseconds per cycle in a graph (1, 4 and 16
+// right-hand sides; "none": launches only), by the most entries a level of
+// the tail may have:
+//                            none   12,000  25,000  49,000
+//   10^4 rows, distance 2      91      83      80      97
+//   the same, 16 rhs          107      95      86      97
+//   32^3 Euler                119     113     113     127
+//   DG 32^2 x 2               124     118     118     124
+//   DG 96^2 x 2               237     225     225     223
+// The rows are bounded by what fits one CU's LDS in FP64; a float tail of
+// more rows gained nothing (96^2 transport: 56 against 59 us).
+constexpr int64_t TAIL_MAX_NNZ = 24576;
+constexpr int32_t TAIL_MAX_ROWS = 4608;
+constexpr int32_t TAIL_MAX_COARSE = 192;     // its inverse is read through one CU too
+constexpr size_t TAIL_MAX_PACK = (size_t)256 << 20;
+
+// LDS of the tail from level t on with w-byte vectors, in bytes (see the
+// kernels for what it holds).
+static size_t tail_lds(const lair_hierarchy *h, size_t t, size_t w, bool transpose) {
+    size_t e = 2 * ((size_t)h->L[t]->n + 1);
+    if (!transpose) e += (size_t)h->L.back()->n + 1;
+    else if (t + 1 < h->L.size()) e += (size_t)h->L[t + 1]->n + 1;
+    for (size_t l = t; l < h->L.size(); ++l) e += (size_t)h->L[l]->n + 1;
+    return e * w;
+}
+
+// First level of the tail of a single system (the number of levels: none).
+static size_t tail_start(const lair_hierarchy *h, size_t w, bool transpose) {
+    const size_t nl = h->L.size();
+    if (h->nsys > 1 || !h->kinv.get() || h->nL > TAIL_MAX_COARSE) return nl;
+    size_t t = nl;
+    const size_t limit = std::min<size_t>(tail_lds_limit(), INT32_MAX);
+    for (size_t l = nl - 1; l-- > 0;) {
+        const Level &Lv = *h->L[l];
+        if ((!transpose && Lv.split) || nl - l > (size_t)TAIL_MAX_LEVELS ||
+            Lv.A.nnz > TAIL_MAX_NNZ || Lv.n > TAIL_MAX_ROWS || tail_lds(h, l, w, transpose) > limit)
+            break;
+        t = l;
+    }
+    return t;
+}
+
+template <class VT>
+static const VT *values(const DevCSR &M) {
+    if constexpr (std::is_same<VT, double>::value) return M.v.get();
+    else return M.v32.get();
+}
+
+template <class VT>
+static std::unique_ptr<TailArgs<VT>> &tail_args(Tail &t) {
+    if constexpr (std::is_same<VT, double>::value) return t.a64;
+    else return t.a32;
+}
+
+// Pack the tail's operators for nrhs right-hand sides (on s).
+template <class VT>
+static Tail make_tail(lair_hierarchy *h, size_t start, int32_t nrhs, bool transpose,
+                      hipStream_t s) {
+    Tail T;
+    const int w = sizeof(VT);
+    T.w = w;
+    T.nrhs = nrhs;
+    T.transpose = transpose;
+    T.start = start;
+    const size_t nl = h->L.size();
+    const int32_t nlv = (int32_t)(nl - start);
+    auto &a = tail_args<VT>(T);
+    a.reset(new TailArgs<VT>());
+    a->nlv = nlv;
+    a->nrhs = nrhs;
+    a->knode = nodal(h->opt) ? h->opt.block_size : 0;
+    a->lds_bytes = (int32_t)tail_lds(h, start, w, transpose);
+    a->omega = (VT)h->opt.omega;
+    a->kinv = h->kinv.get();
+    T.bytes = 8.0 * h->coarse_entries + 2.0 * w * nrhs * h->nL;
+    T.flops = 2.0 * h->coarse_entries * nrhs;
+    // longest rows: the transposes have to be measured
+    std::vector<int32_t> longest(3 * (size_t)nlv, 0);
+    if (transpose) {
+        std::vector<const int32_t *> rp;
+        std::vector<int32_t> n;
+        for (int32_t k = 0; k + 1 < nlv; ++k) {
+            Level &Lv = *h->L[start + k];
+            for (const DevCSR *M : {&Lv.At, &Lv.Pt, &Lv.Rt}) {
+                rp.push_back(M->rp.get());
+                n.push_back(M->nrows);
+            }
+        }
+        max_rows((int)rp.size(), rp.data(), n.data(), longest.data(), s);
+    }
+    std::vector<TailSources<VT>> src((size_t)nlv);
+    size_t total = 0;
+    for (int32_t k = 0; k < nlv; ++k) {
+        Level &Lv = *h->L[start + k];
+        TailLevel<VT> &o = a->lv[k];
+        o.n = Lv.n;
+        if (k + 1 == nlv) break;
+        o.nf = Lv.nf;
+        o.nc = Lv.nc;
+        if (nodal(h->opt)) o.dinv = Lv.ndinv.get();
+        const DevCSR &A = transpose ? Lv.At : Lv.A;
+        const DevCSR &R = transpose ? Lv.Pt : Lv.R, &P = transpose ? Lv.Rt : Lv.P;
+        const int32_t ta = transpose ? Lv.team_At : Lv.team_A;
+        const int32_t la = transpose ? longest[3 * k] : Lv.max_row;
+        const int32_t lr = transpose ? longest[3 * k + 1] : Lv.st.s_max + 1;
+        // a row of P has one entry, or some of its row of A and itself
+        const int32_t lp = transpose ? longest[3 * k + 2]
+                           : h->opt.interp == LAIR_P_ONE_POINT ? 1 : Lv.max_row;
+        for (int t = 0; t < TAIL_SETS; ++t) {
+            TailSource<VT> &S = src[k].src[t];
+            // the residual of every row: the transposed cycle's, and that of
+            // an iterate given to the first level
+            if (t == TAIL_A && !transpose && (w == 4 || k > 0 || start > 0)) continue;
+            const DevCSR &M = t == TAIL_R ? R : t == TAIL_P ? P : A;
+            const int32_t len = t == TAIL_R ? lr : t == TAIL_P ? lp : la;
+            const int32_t team = t == TAIL_R ? (transpose ? Lv.team_Pt : Lv.team_R)
+                                 : t == TAIL_P ? (transpose ? Lv.team_Rt : Lv.team_P) : ta;
+            S.rp = M.rp.get();
+            S.cj = M.cj.get();
+            S.v = values<VT>(M);
+            const bool sweep = t == TAIL_F || t == TAIL_C;
+            if (sweep && nodal(h->opt)) S.v = vec<VT>(Lv.av, Lv.av32);
+            S.rows = t == TAIL_F ? Lv.flist.get() : t == TAIL_C ? Lv.clist.get() : nullptr;
+            S.n = t == TAIL_F ? Lv.nf : t == TAIL_C ? Lv.nc : M.nrows;
+            S.ncol = M.ncols;
+            S.diag = sweep;
+            cycle_team(team, nrhs, w, sweep, &S.lg, &S.ll);
+            S.nchunk = tail_chunks(S.n, S.lg);
+            S.dst.lg = S.lg;
+            // one entry a lane: one-point interpolation
+            S.dst.u4 = t != TAIL_P || tail_groups(len, S.lg, S.ll, false) > 1;
+            const int32_t g = tail_groups(len, S.lg, S.ll, S.dst.u4);
+            if (g > UINT16_MAX) return Tail();
+            S.dst.smax = (uint16_t)g;
+            total = tail_layout(S.dst, total, S.nchunk, sweep, w);
+        }
+        T.bytes += ab_rowdot(Lv.R, w, nrhs, 1) + ab_rowdot(Lv.P, w, nrhs, 1) +
+                   2.0 * ab_jacobi(Lv.nnzF, Lv.nf, Lv.n, w, nrhs, false) +
+                   ab_jacobi(Lv.nnzC, Lv.nc, Lv.n, w, nrhs, false) +
+                   (transpose ? ab_rowdot(Lv.A, w, nrhs, 2) : 0.0);
+        T.flops += 2.0 * nrhs * ((double)Lv.R.nnz + Lv.P.nnz + 2.0 * Lv.nnzF + Lv.nnzC +
+                                 (transpose ? Lv.A.nnz : 0));
+    }
+    if (total > TAIL_MAX_PACK) return Tail();
+    T.blob.alloc(std::max<size_t>(total, 256), s);
+    a->blob = T.blob.get();
+    for (int32_t k = 0; k + 1 < nlv; ++k) {
+        src[k].blob = T.blob.get();
+        for (int t = 0; t < TAIL_SETS; ++t) a->lv[k].set[t] = src[k].src[t].dst;
+        launch_tail_pack<VT>(src[k], s);
+    }
+    return T;
+}
+
+// The tail a cycle of this kind uses from level l on, or nullptr.
+template <class VT>
+static Tail *find_tail(lair_hierarchy *h, int32_t nrhs, bool transpose, size_t l) {
+    for (auto &t : h->tails)
+        if (t.w == (int)sizeof(VT) && t.nrhs == nrhs && t.transpose == transpose)
+            return l >= t.start && tail_args<VT>(t) ? &t : nullptr;
+    return nullptr;
+}
+
+// Make the tail of a cycle kind if there is none yet.  Not while the stream
+// is captured: the cycle then runs launch by launch, the same sums.
+static void ensure_tail(lair_hierarchy *h, int32_t nrhs, bool mixed, bool transpose,
+                        hipStream_t s) {
+    const int w = mixed ? 4 : 8;
+    for (auto &t : h->tails)
+        if (t.w == w && t.nrhs == nrhs && t.transpose == transpose) return;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return;
+    }
+    const size_t start = tail_start(h, w, transpose);
+    Tail T;
+    if (start < h->L.size())
+        T = mixed ? make_tail<float>(h, start, nrhs, transpose, s)
+                  : make_tail<double>(h, start, nrhs, transpose, s);
+    T.w = w;
+    T.nrhs = nrhs;
+    T.transpose = transpose;
+    h->drop_graphs();        // captured without it
+    h->tails.push_back(std::move(T));
+}
+
 // V-cycle from level l.  With x_zero the incoming iterate is zero: the
 // residual is b itself and the interpolated correction is assigned.  When
 // r is non-null it already holds b - A x.  With split_out the result may be
@@ -173,6 +366,12 @@ static const VT *vcycle(lair_hierarchy *h, size_t l, const VT *b, VT *x, bool x_
     const int w = sizeof(VT);
     if (l + 1 == h->L.size()) {
         coarse_solve<VT>(h, b, x, nrhs, false, s);
+        return nullptr;
+    }
+    if (Tail *T = h->use_act ? nullptr : find_tail<VT>(h, nrhs, false, l)) {
+        ProfScope ps("tail", s, T->bytes, T->flops);
+        launch_tail<VT>(*tail_args<VT>(*T), x_zero ? TAIL_ZERO : r ? TAIL_RESID : TAIL_ITERATE,
+                        b, x, r, s);
         return nullptr;
     }
     Level &Nx = *h->L[l + 1];
@@ -244,6 +443,11 @@ static void vcycle_t(lair_hierarchy *h, size_t l, const double *g, double *lam,
         coarse_solve<double>(h, g, lam, nrhs, true, s);
         return;
     }
+    if (Tail *T = lam_zero ? find_tail<double>(h, nrhs, true, l) : nullptr) {
+        ProfScope ps("tail", s, T->bytes, T->flops);
+        launch_tail_t(*T->a64, g, lam, s);
+        return;
+    }
     if (lam_zero) op_fill<double>(lam, 0.0, (int64_t)Lv.n * nrhs, s);
     CsrView<double> At = view<double>(Lv.At, Lv.team_At);
     double om = h->opt.omega;
@@ -298,7 +502,8 @@ static void norms_host(lair_hierarchy *h, const double *r, int32_t nrhs,
 enum { IT_FP64 = 0, IT_MIXED = 1, IT_BATCH_FP64 = 2, IT_BATCH_MIXED = 3 };
 
 static const char *const CYCLE_CATEGORIES[] = {
-    "jacobi", "scatter", "residual", "restrict", "interpolate", "coarse_solve", "norm", "cast"};
+    "jacobi", "scatter", "residual", "restrict", "interpolate", "coarse_solve", "norm", "cast",
+    "tail"};
 
 // Iterations are captured unless the caller asked for eager launches or the
 // profiler times one of the cycle's categories (its events would have to be
@@ -388,6 +593,7 @@ lair_status solve_impl(lair_hierarchy *h, const double *b, double *x,
     check_nrhs(h, nrhs);
     ensure_vectors(h, nrhs, s);
     if (transpose) ensure_transposes(h);
+    ensure_tail(h, nrhs, h->opt.precision == LAIR_MIXED && !transpose, transpose, s);
     Level &L0 = *h->L[0];
     const int64_t n = L0.n;
     const double *bb = b;
@@ -521,6 +727,7 @@ lair_status solve_fgmres_impl(lair_hierarchy *h, const double *b, double *x,
     if (h->batch) fail(LAIR_EUNSUPPORTED, "FGMRES is for a single system");
     if (m < 1 || m > 64) fail(LAIR_EINVAL, "restart must be in [1, 64] (got %d)", m);
     ensure_vectors(h, nrhs, s);
+    ensure_tail(h, nrhs, h->opt.precision == LAIR_MIXED, false, s);
     Level &L0 = *h->L[0];
     const int64_t n = L0.n;
     const int32_t R = nrhs;
@@ -717,6 +924,7 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     check_solve_args(h, b, x, rtol, maxit);
     if (!h->batch) fail(LAIR_EINVAL, "the hierarchy was not built by lair_setup_batch");
     ensure_vectors(h, 1, s);
+    ensure_tail(h, 1, h->opt.precision == LAIR_MIXED, false, s);
     Level &L0 = *h->L[0];
     const int32_t ns = h->nsys;
     const int64_t n = L0.n;
@@ -990,6 +1198,7 @@ void cycle_impl(lair_hierarchy *h, const double *b, double *x, int32_t nrhs, hip
     if (!h || !b || !x) fail(LAIR_EINVAL, "NULL argument");
     check_nrhs(h, nrhs);
     ensure_vectors(h, nrhs, s);
+    ensure_tail(h, nrhs, h->opt.precision == LAIR_MIXED, false, s);
     cycle_body(h, b, x, nrhs, s);
 }
 
@@ -1027,6 +1236,7 @@ void cycle_transpose_impl(lair_hierarchy *h, const double *g, double *lam, int32
     if (nodal(h->opt)) fail(LAIR_EUNSUPPORTED, "transposed cycle on a nodal hierarchy");
     ensure_vectors(h, nrhs, s);
     ensure_transposes(h);
+    ensure_tail(h, nrhs, false, true, s);
     // lam <- lam + B^T (g - A^T lam)
     Level &L0 = *h->L[0];
     int64_t n = L0.n;
