@@ -45,10 +45,11 @@ struct Level {
     DevArr<uint8_t> stopped_dev;
     DevArr<int32_t> rclist;
     int32_t nrc = -1;                 // -1: relax every C row (clist)
-    // rows of the systems still iterated (batch solve): all rows, F rows,
-    // relaxed C rows; their lengths in act_cnt[0..2] on the device (inside
-    // the hierarchy's list upload area)
-    DevArr<int32_t> act_rows, act_f, act_c;
+    // rows of the systems still iterated (batch solve): the rows that take a
+    // residual or a restriction; the F rows, relaxed C rows and interpolated
+    // rows of the systems whose tail starts further down; their lengths in
+    // act_cnt[0..3] on the device (inside the hierarchy's list upload area)
+    DevArr<int32_t> act_rows, act_f, act_c, act_p;
     int32_t *act_cnt = nullptr;
     // cycle work vectors (capacity h->nrhs_cap right-hand sides)
     DevArr<double> b, x, t, r;
@@ -82,6 +83,10 @@ struct Tail {
     std::unique_ptr<TailArgs<double>> a64;
     std::unique_ptr<TailArgs<float>> a32;
     double bytes = 0.0, flops = 0.0;   // algorithmic, of its levels
+    // batch: the level each system's tail starts at; `start` is the last of
+    // them, where the tail is launched
+    std::vector<int32_t> top;
+    DevArr<int32_t> tables;
 };
 
 }  // namespace lair
@@ -143,6 +148,7 @@ struct lair_hierarchy {
     }
     // packed tails, made when a cycle first asks for one (new values: cleared)
     std::vector<lair::Tail> tails;
+    std::unique_ptr<lair::Tail> batch_tail;  // of a batch solve
     ~lair_hierarchy() {
         drop_graphs();
         if (gstream) (void)hipStreamDestroy(gstream);

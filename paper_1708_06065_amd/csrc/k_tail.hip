@@ -147,11 +147,18 @@ __device__ __forceinline__ void lds_barrier() {
 
 // A row set of one level for one system: the parts of its blob (byte
 // addresses, the system's first chunk applied) and its rows.
+// (addresses read from a table: the compiler must be told that they are in
+// global memory, or it loads through the flat path, which counts against LDS
+// and stalls the barriers)
+#define LAIR_GLOBAL __attribute__((address_space(1)))
+using GlobalBytes = const LAIR_GLOBAL char *;
 struct RowSet {
-    const char *used, *row, *diag, *col, *val;
+    GlobalBytes used, row, diag, col, val;
     int n, lg, smax;
     bool u4;
 };
+
+using u32x2 = ExtVec<uint32_t, 2>;
 
 // Four entries of a lane's share (columns packed two to a word).
 template <class VT>
@@ -174,27 +181,27 @@ __device__ __forceinline__ Group<VT> load_group(const RowSet &S, int ch, int grp
     const uint32_t lane = threadIdx.x & (WAVE - 1);
     const uint32_t o = (uint32_t)(ch * S.smax + grp) * WAVE + lane;
     if (U4) {
-        const uint2 cc = *reinterpret_cast<const uint2 *>(S.col + (size_t)(o * 8u));
+        const u32x2 cc = *reinterpret_cast<const LAIR_GLOBAL u32x2 *>(S.col + (size_t)(o * 8u));
         G.c01 = cc.x;
         G.c23 = cc.y;
-        const char *pv = S.val + (size_t)(o * (uint32_t)(4 * sizeof(VT)));
+        GlobalBytes pv = S.val + (size_t)(o * (uint32_t)(4 * sizeof(VT)));
         if constexpr (sizeof(VT) == 4) {
-            const float4 v = *reinterpret_cast<const float4 *>(pv);
+            const ExtVec<float, 4> v = *reinterpret_cast<const LAIR_GLOBAL ExtVec<float, 4> *>(pv);
             G.a0 = v.x;
             G.a1 = v.y;
             G.a2 = v.z;
             G.a3 = v.w;
         } else {
-            const double2 v0 = reinterpret_cast<const double2 *>(pv)[0];
-            const double2 v1 = reinterpret_cast<const double2 *>(pv)[1];
+            const ExtVec<double, 2> v0 = reinterpret_cast<const LAIR_GLOBAL ExtVec<double, 2> *>(pv)[0];
+            const ExtVec<double, 2> v1 = reinterpret_cast<const LAIR_GLOBAL ExtVec<double, 2> *>(pv)[1];
             G.a0 = v0.x;
             G.a1 = v0.y;
             G.a2 = v1.x;
             G.a3 = v1.y;
         }
     } else {
-        G.c01 = *reinterpret_cast<const uint16_t *>(S.col + (size_t)(o * 2u));
-        G.a0 = *reinterpret_cast<const VT *>(S.val + (size_t)(o * (uint32_t)sizeof(VT)));
+        G.c01 = *reinterpret_cast<const LAIR_GLOBAL uint16_t *>(S.col + (size_t)(o * 2u));
+        G.a0 = *reinterpret_cast<const LAIR_GLOBAL VT *>(S.val + (size_t)(o * (uint32_t)sizeof(VT)));
     }
     return G;
 }
@@ -220,10 +227,10 @@ template <class VT, bool DIAG, bool U4>
 __device__ __forceinline__ void load_head(const RowSet &S, int ch, Head<VT> &h) {
     if (ch << (6 - S.lg) >= S.n) return;
     const uint32_t o = (uint32_t)ch * WAVE + (threadIdx.x & (WAVE - 1));
-    h.used = *reinterpret_cast<const uint16_t *>(S.used + 2 * (size_t)ch);
+    h.used = *reinterpret_cast<const LAIR_GLOBAL uint16_t *>(S.used + 2 * (size_t)ch);
     if (DIAG) {
-        h.row = *reinterpret_cast<const uint16_t *>(S.row + (size_t)(o * 2u));
-        h.d = *reinterpret_cast<const VT *>(S.diag + (size_t)(o * (uint32_t)sizeof(VT)));
+        h.row = *reinterpret_cast<const LAIR_GLOBAL uint16_t *>(S.row + (size_t)(o * 2u));
+        h.d = *reinterpret_cast<const LAIR_GLOBAL VT *>(S.diag + (size_t)(o * (uint32_t)sizeof(VT)));
     }
     h.g = load_group<VT, U4>(S, ch, 0);
 }
@@ -297,10 +304,21 @@ __device__ __forceinline__ void row_phase(const RowSet &S, const Head<VT> &h, co
     set_phase<VT, MULTI, DIAG, GATHER, true>(S, h, src, fin);
 }
 
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <class T>
+__device__ __forceinline__ T *uniform_ptr(T *p) {
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return reinterpret_cast<T *>((uint64_t)hi << 32 | lo);
+}
+
 // x = M b for the dense m x m inverse M (rows, or columns with TRANS), TC
 // lanes per output, in double whatever the vector type.
 template <class VT, int TC, bool TRANS>
-__device__ __forceinline__ void dense_phase(int m, const double *M, const VT *b, VT *x) {
+__device__ __forceinline__ void dense_phase(int m, const double *Mp, const VT *b, VT *x) {
+    const LAIR_GLOBAL double *M = (const LAIR_GLOBAL double *)uniform_ptr(Mp);
+    m = uniform(m);
     const int lane = threadIdx.x % TC;
     for (int i = threadIdx.x / TC; i < m; i += TAIL_BS / TC) {
         double acc = 0.0;
@@ -323,15 +341,6 @@ __device__ __forceinline__ void stage_args(const TailArgs<VT> &a, TailArgs<VT> &
         reinterpret_cast<uint64_t *>(&s)[threadIdx.x] =
             reinterpret_cast<const uint64_t *>(&a)[threadIdx.x];
     __syncthreads();
-}
-
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-template <class T>
-__device__ __forceinline__ T *uniform_ptr(T *p) {
-    const uint64_t u = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-    return reinterpret_cast<T *>((uint64_t)hi << 32 | lo);
 }
 
 // The system's (or the single system's) place on every level.
@@ -376,7 +385,7 @@ __device__ __forceinline__ void tail_map(const TailArgs<VT> &a, int q, int top, 
 template <class VT>
 __device__ __forceinline__ RowSet row_set(const TailArgs<VT> &a, const TailMap &m, int l, int t) {
     const TailSet &T = a.lv[l].set[t];
-    const char *blob = uniform_ptr(a.blob);
+    GlobalBytes blob = (GlobalBytes)uniform_ptr(a.blob);
     RowSet S;
     S.lg = uniform(T.lg);
     S.smax = uniform(T.smax);
@@ -405,12 +414,12 @@ k_tail(const TailArgs<VT> args, const VT *b, VT *x, const VT *r) {
     if (BATCH && args.active && !args.active[args.order[blockIdx.x]]) return;
     stage_args(args, a);
     VT *const W = reinterpret_cast<VT *>(tail_lds);
-    const int q = BATCH ? a.order[blockIdx.x] : 0;
-    const int rhs = BATCH ? 0 : blockIdx.x, R = BATCH ? 1 : a.nrhs;
-    const int top = BATCH ? a.top[q] : 0;
-    const int last = (BATCH ? a.slev[q] : a.nlv) - 1;
+    const int q = BATCH ? uniform(args.order[blockIdx.x]) : 0;
+    const int rhs = BATCH ? 0 : blockIdx.x, R = BATCH ? 1 : args.nrhs;
+    const int top = BATCH ? uniform(args.top[q]) : 0;
+    const int last = (BATCH ? uniform(args.slev[q]) : args.nlv) - 1;
     tail_map(a, q, top, last, 2, mp);
-    const int n0 = mp.n[top], r0 = mp.row0[top];
+    const int n0 = uniform(mp.n[top]), r0 = uniform(mp.row0[top]);
     VT *const X = W, *const Y = W + n0 + 1, *const B0 = W + 2 * (n0 + 1);
     // the zeros after the vectors (a level's X and Y end at its own size: see
     // the interpolation)
@@ -419,8 +428,8 @@ k_tail(const TailArgs<VT> args, const VT *b, VT *x, const VT *r) {
         if (l == last) W[mp.off[l] + 2 * mp.n[l] + 1] = (VT)0;
     }
     if (threadIdx.x == 0) X[n0] = Y[n0] = (VT)0;
-    const VT *bt = BATCH ? a.lv[top].vb : b;
-    VT *xt = BATCH ? a.lv[top].vx : x;
+    const LAIR_GLOBAL VT *bt = (const LAIR_GLOBAL VT *)uniform_ptr(BATCH ? a.lv[top].vb : b);
+    LAIR_GLOBAL VT *xt = (LAIR_GLOBAL VT *)uniform_ptr(BATCH ? a.lv[top].vx : x);
     Head<VT> p;
     RowSet S;
     if (top < last) {
@@ -446,8 +455,8 @@ k_tail(const TailArgs<VT> args, const VT *b, VT *x, const VT *r) {
         // the next set: the restriction below, or the first interpolation
         const bool down = l + 1 < last;
         const RowSet SN = row_set(a, mp, down ? l + 1 : l, down ? TAIL_R : TAIL_P);
-        const VT *src = (MODE != TAIL_ZERO && l == top) ? Y : W + mp.off[l];
-        VT *dst = W + mp.off[l + 1];
+        const VT *src = (MODE != TAIL_ZERO && l == top) ? Y : W + uniform(mp.off[l]);
+        VT *dst = W + uniform(mp.off[l + 1]);
         Head<VT> pn;
         lds_barrier();
         if (down) load_ahead<VT, false>(SN, pn);
@@ -457,25 +466,26 @@ k_tail(const TailArgs<VT> args, const VT *b, VT *x, const VT *r) {
         p = pn;
     }
     {
-        const int m = mp.n[last];
-        VT *bl = W + mp.off[last], *out = bl + m + 1;
+        const int m = uniform(mp.n[last]);
+        VT *bl = W + uniform(mp.off[last]), *out = bl + m + 1;
         lds_barrier();
         if (BATCH) dense_phase<VT, WAVE, false>(m, a.binv + a.doff[q], bl, out);
         else dense_phase<VT, 16, false>(m, a.kinv, bl, out);
     }
     const VT om = a.omega;
     for (int l = last - 1; l >= top; --l) {
-        VT *bl = W + mp.off[l];
-        const VT *e = W + mp.off[l + 1] + (l + 1 == last ? mp.n[last] + 1 : 0);
+        VT *bl = W + uniform(mp.off[l]);
+        const VT *e = W + uniform(mp.off[l + 1] + (l + 1 == last ? mp.n[last] + 1 : 0));
         const bool add = MODE != TAIL_ZERO && l == top;
         const RowSet SF = row_set(a, mp, l, TAIL_F);
-        if (a.knode) {
+        if (args.knode) {
             // the sweeps' right-hand side D^{-1} b
-            const int kn = a.knode, n = mp.n[l];
-            const double *dinv = a.lv[l].dinv;
+            const int kn = args.knode, n = uniform(mp.n[l]);
+            const LAIR_GLOBAL double *dinv =
+                (const LAIR_GLOBAL double *)uniform_ptr(a.lv[l].dinv);
             lds_barrier();
             for (int i = threadIdx.x; i < n; i += TAIL_BS) {
-                const double *d = dinv + (size_t)i * kn;
+                const LAIR_GLOBAL double *d = dinv + (size_t)i * kn;
                 const VT *bb = bl + i / kn * kn;
                 double acc = 0.0;
                 for (int c = 0; c < kn; ++c) acc += d[c] * (double)bb[c];
@@ -533,9 +543,9 @@ k_tail_t(const TailArgs<double> args, const double *g, double *lam) {
     __shared__ TailArgs<double> a;
     stage_args(args, a);
     double *const W = reinterpret_cast<double *>(tail_lds);
-    const int rhs = blockIdx.x, R = a.nrhs, last = a.nlv - 1;
+    const int rhs = blockIdx.x, R = args.nrhs, last = args.nlv - 1;
     tail_map(a, 0, 0, last, 3, mp);
-    const int n0 = mp.n[0];
+    const int n0 = uniform(mp.n[0]);
     double *const Y = W, *const Ba = W + n0 + 1, *const Bb = W + 2 * (n0 + 1);
     RowSet SC = row_set(a, mp, 0, TAIL_C);
     Head<double> pc;
@@ -543,9 +553,9 @@ k_tail_t(const TailArgs<double> args, const double *g, double *lam) {
     for (int i = threadIdx.x; i < n0; i += TAIL_BS) Ba[i] = g[(size_t)i * R + rhs];
     const double om = a.omega;
     for (int l = 0; l < last; ++l) {
-        double *X = W + mp.off[l], *bl = l & 1 ? Bb : Ba, *bn = l & 1 ? Ba : Bb;
+        double *X = W + uniform(mp.off[l]), *bl = l & 1 ? Bb : Ba, *bn = l & 1 ? Ba : Bb;
         const RowSet SF = row_set(a, mp, l, TAIL_F);
-        const int n = mp.n[l];
+        const int n = uniform(mp.n[l]);
         for (int i = threadIdx.x; i <= n; i += TAIL_BS) X[i] = 0.0;
         if (threadIdx.x == 0) Y[n] = bl[n] = 0.0;
         Head<double> pf, pa, pr;
@@ -589,8 +599,8 @@ k_tail_t(const TailArgs<double> args, const double *g, double *lam) {
     dense_phase<double, 16, true>(mp.n[last], a.kinv, last & 1 ? Bb : Ba, W + mp.off[last]);
     if (threadIdx.x == 0) W[mp.off[last] + mp.n[last]] = 0.0;
     for (int l = last - 1; l >= 0; --l) {
-        double *X = W + mp.off[l];
-        const double *e = W + mp.off[l + 1];
+        double *X = W + uniform(mp.off[l]);
+        const double *e = W + uniform(mp.off[l + 1]);
         const RowSet SN = row_set(a, mp, std::max(l - 1, 0), TAIL_P);
         Head<double> pn;
         lds_barrier();

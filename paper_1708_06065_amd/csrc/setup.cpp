@@ -1442,6 +1442,7 @@ void update_diag_impl(lair_hierarchy *h, const double *diag, int32_t on_device,
     LAIR_LAUNCH_CHECK();
     h->drop_graphs();
     h->tails.clear();
+    h->batch_tail.reset();
     h->have_transpose = false;
     h->n_singular = 0;
     DevArr<int64_t> tmp;

@@ -182,6 +182,7 @@ constexpr int64_t TAIL_MAX_NNZ = 24576;
 constexpr int32_t TAIL_MAX_ROWS = 4608;
 constexpr int32_t TAIL_MAX_COARSE = 192;     // its inverse is read through one CU too
 constexpr size_t TAIL_MAX_PACK = (size_t)256 << 20;
+constexpr size_t TAIL_MAX_BATCH_PACK = (size_t)2 << 30;
 
 // LDS of the tail from level t on with w-byte vectors, in bytes (see the
 // kernels for what it holds).
@@ -354,6 +355,162 @@ static void ensure_tail(lair_hierarchy *h, int32_t nrhs, bool mixed, bool transp
     h->tails.push_back(std::move(T));
 }
 
+// The tail of a batch solve: one workgroup per system, from the first level
+// at which the system is as small as a single system's tail may be (its
+// entries taken from the union's mean row).  Systems of a batch differ by a
+// factor of a hundred, so each has a start of its own; the levels above are
+// launched over the systems that still need them, and the tail is launched
+// where the last system's starts.  nullptr: no tail (a coarsest block without
+// an inverse, too many levels).
+template <class VT>
+static std::unique_ptr<Tail> make_batch_tail(lair_hierarchy *h,
+                                             const std::vector<std::array<std::vector<int32_t>, 3>> &runs,
+                                             hipStream_t s) {
+    const int w = sizeof(VT);
+    const int32_t ns = h->nsys, nl = (int32_t)h->L.size();
+    const std::vector<int64_t> &cs = h->L.back()->seg;
+    if (nl > TAIL_MAX_LEVELS || !h->binv.get()) return nullptr;
+    for (int32_t q = 0; q < ns; ++q)
+        if (cs[q + 1] - cs[q] > mid_dense_max()) return nullptr;
+    auto rows = [&](int32_t l, int32_t q) {
+        return (int64_t)(h->L[l]->seg[q + 1] - h->L[l]->seg[q]);
+    };
+    std::unique_ptr<Tail> T(new Tail());
+    T->w = w;
+    T->nrhs = 1;
+    T->top.assign((size_t)ns, 0);
+    const size_t limit = std::min<size_t>(tail_lds_limit(), INT32_MAX);
+    size_t lds = 0;
+    int32_t depth = 0;
+    for (int32_t q = 0; q < ns; ++q) {
+        const int32_t last = h->sys_levels[q] - 1;
+        size_t below = 2 * ((size_t)rows(last, q) + 1);     // coarsest vectors
+        int32_t t = last;
+        for (int32_t l = last - 1; l >= 0; --l) {
+            const int64_t n = rows(l, q);
+            const double mean = (double)h->L[l]->A.nnz / std::max(h->L[l]->n, 1);
+            below += (size_t)n + 1;
+            if (n > TAIL_MAX_ROWS || n * mean > (double)TAIL_MAX_NNZ ||
+                (below + 2 * ((size_t)n + 1)) * w > limit)
+                break;
+            t = l;
+        }
+        size_t e = 2 * ((size_t)rows(t, q) + 1) + (size_t)rows(last, q) + 1;
+        for (int32_t l = t; l <= last; ++l) e += (size_t)rows(l, q) + 1;
+        if (e * w > limit) return nullptr;
+        lds = std::max(lds, e * w);
+        T->top[q] = t;
+        depth = std::max(depth, t);
+    }
+    T->start = (size_t)depth;
+    auto &a = tail_args<VT>(*T);
+    a.reset(new TailArgs<VT>());
+    a->nlv = nl;
+    a->nrhs = 1;
+    a->nsys = ns;
+    a->lds_bytes = (int32_t)lds;
+    a->omega = (VT)h->opt.omega;
+    a->doff = h->dense_off.get();
+    a->binv = h->binv.get();
+    a->active = h->active_dev.get();
+    // tables: order, top, levels, then per level the F and C runs and the
+    // first chunks of every set
+    const size_t per = (size_t)ns + 1, lvt = (2 + TAIL_SETS) * per;
+    std::vector<int32_t> tab(3 * (size_t)ns + lvt * (size_t)nl, 0);
+    std::vector<int32_t> order((size_t)ns);
+    for (int32_t q = 0; q < ns; ++q) order[q] = q;
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+        return rows(T->top[x], x) > rows(T->top[y], y);
+    });
+    std::copy(order.begin(), order.end(), tab.begin());
+    std::copy(T->top.begin(), T->top.end(), tab.begin() + ns);
+    std::copy(h->sys_levels.begin(), h->sys_levels.end(), tab.begin() + 2 * ns);
+    T->tables.alloc(tab.size(), s);
+    const int32_t *d = T->tables.get();
+    a->order = d;
+    a->top = d + ns;
+    a->slev = d + 2 * ns;
+    T->bytes = 8.0 * h->coarse_entries + 2.0 * w * h->nL;
+    T->flops = 2.0 * h->coarse_entries;
+    std::vector<TailSources<VT>> src((size_t)nl);
+    size_t total = 0;
+    for (int32_t l = 0; l < nl; ++l) {
+        Level &Lv = *h->L[l];
+        TailLevel<VT> &o = a->lv[l];
+        o.n = Lv.n;
+        o.seg = Lv.seg_dev.get();
+        if (l + 1 == nl) break;
+        Level &Nx = *h->L[l + 1];
+        o.nf = Lv.nf;
+        o.nc = Lv.nrc >= 0 ? Lv.nrc : Lv.nc;
+        int32_t *t0 = tab.data() + 3 * ns + lvt * l;
+        const int32_t *d0 = d + 3 * ns + lvt * l;
+        std::copy(runs[l][1].begin(), runs[l][1].end(), t0);
+        std::copy(runs[l][2].begin(), runs[l][2].end(), t0 + per);
+        o.frun = d0;
+        o.crun = d0 + per;
+        o.chunk0 = d0 + 2 * per;
+        for (int t = 0; t < TAIL_A; ++t) {
+            TailSource<VT> &S = src[l].src[t];
+            const DevCSR &M = t == TAIL_R ? Lv.R : t == TAIL_P ? Lv.P : Lv.A;
+            const int32_t len = t == TAIL_R ? Lv.st.s_max + 1
+                                : t == TAIL_P && h->opt.interp == LAIR_P_ONE_POINT ? 1
+                                                                                  : Lv.max_row;
+            const bool sweep = t == TAIL_F || t == TAIL_C;
+            S.rp = M.rp.get();
+            S.cj = M.cj.get();
+            S.v = values<VT>(M);
+            S.rows = t == TAIL_F ? Lv.flist.get()
+                     : t == TAIL_C ? (Lv.nrc >= 0 ? Lv.rclist.get() : Lv.clist.get()) : nullptr;
+            S.run = t == TAIL_F ? o.frun : o.crun;
+            S.rseg = t == TAIL_R ? Nx.seg_dev.get() : Lv.seg_dev.get();
+            S.cseg = t == TAIL_P ? Nx.seg_dev.get() : Lv.seg_dev.get();
+            S.chunk0 = o.chunk0 + t * per;
+            S.nsys = ns;
+            S.diag = sweep;
+            cycle_team(t == TAIL_R ? Lv.team_R : t == TAIL_P ? Lv.team_P : Lv.team_A, 1, w,
+                       sweep, &S.lg, &S.ll);
+            S.dst.lg = S.lg;
+            S.dst.u4 = t != TAIL_P || tail_groups(len, S.lg, S.ll, false) > 1;
+            const int32_t g = tail_groups(len, S.lg, S.ll, S.dst.u4);
+            if (g > UINT16_MAX) return nullptr;
+            S.dst.smax = (uint16_t)g;
+            int32_t *c0 = t0 + (2 + t) * per;
+            for (int32_t q = 0; q < ns; ++q) {
+                int32_t n = 0;
+                if (l >= T->top[q] && l + 1 < h->sys_levels[q])
+                    n = t == TAIL_R ? (int32_t)rows(l + 1, q) : t == TAIL_P ? (int32_t)rows(l, q)
+                        : runs[l][t == TAIL_F ? 1 : 2][q + 1] - runs[l][t == TAIL_F ? 1 : 2][q];
+                c0[q + 1] = c0[q] + tail_chunks(n, S.lg);
+            }
+            S.nchunk = c0[ns];
+            total = tail_layout(S.dst, total, S.nchunk, sweep, w);
+        }
+        double share = 0.0;
+        for (int32_t q = 0; q < ns; ++q)
+            if (l >= T->top[q] && l + 1 < h->sys_levels[q]) share += (double)rows(l, q);
+        share /= std::max(Lv.n, 1);
+        T->bytes += share * (ab_rowdot(Lv.R, w, 1, 1) + ab_rowdot(Lv.P, w, 1, 1) +
+                             2.0 * ab_jacobi(Lv.nnzF, Lv.nf, Lv.n, w, 1, false) +
+                             ab_jacobi(Lv.nnzC, o.nc, Lv.n, w, 1, false));
+        T->flops += share * 2.0 * ((double)Lv.R.nnz + Lv.P.nnz + 2.0 * Lv.nnzF + Lv.nnzC);
+    }
+    if (total > TAIL_MAX_BATCH_PACK) return nullptr;
+    int32_t *st = (int32_t *)pinned_upload(sizeof(int32_t) * tab.size());
+    memcpy(st, tab.data(), sizeof(int32_t) * tab.size());
+    LAIR_HIP(hipMemcpyAsync(T->tables.get(), st, sizeof(int32_t) * tab.size(),
+                            hipMemcpyHostToDevice, s));
+    T->blob.alloc(std::max<size_t>(total, 256), s);
+    a->blob = T->blob.get();
+    for (int32_t l = 0; l + 1 < nl; ++l) {
+        src[l].blob = T->blob.get();
+        for (int t = 0; t < TAIL_A; ++t) a->lv[l].set[t] = src[l].src[t].dst;
+        launch_tail_pack<VT>(src[l], s);
+    }
+    LAIR_HIP(hipStreamSynchronize(s));     // the staging area is reused
+    return T;
+}
+
 // V-cycle from level l.  With x_zero the incoming iterate is zero: the
 // residual is b itself and the interpolated correction is assigned.  When
 // r is non-null it already holds b - A x.  With split_out the result may be
@@ -364,6 +521,12 @@ static const VT *vcycle(lair_hierarchy *h, size_t l, const VT *b, VT *x, bool x_
                         const VT *r, int32_t nrhs, hipStream_t s, bool split_out = false) {
     Level &Lv = *h->L[l];
     const int w = sizeof(VT);
+    if (h->use_act && h->batch_tail && l == h->batch_tail->start) {
+        Tail &T = *h->batch_tail;
+        ProfScope ps("tail", s, T.bytes, T.flops);
+        launch_tail<VT>(*tail_args<VT>(T), TAIL_ZERO, nullptr, nullptr, nullptr, s);
+        return nullptr;
+    }
     if (l + 1 == h->L.size()) {
         coarse_solve<VT>(h, b, x, nrhs, false, s);
         return nullptr;
@@ -406,8 +569,8 @@ static const VT *vcycle(lair_hierarchy *h, size_t l, const VT *b, VT *x, bool x_
         ProfScope ps("interpolate", s, ab_rowdot(Lv.P, w, nrhs, x_zero ? 1 : 2),
                      2.0 * Lv.P.nnz * nrhs);
         if (h->use_act)
-            op_rowdot_list<VT>(view<VT>(Lv.P, Lv.team_P), x_zero ? 1 : 2, Lv.act_rows.get(),
-                               Lv.act_cnt, Lv.n, xc, nullptr, x, s);
+            op_rowdot_list<VT>(view<VT>(Lv.P, Lv.team_P), x_zero ? 1 : 2, Lv.act_p.get(),
+                               Lv.act_cnt + 3, Lv.n, xc, nullptr, x, s);
         else
             op_spmv<VT>(view<VT>(Lv.Ps.rp.get() ? Lv.Ps : Lv.P, Lv.team_P), xc, x, nrhs, !x_zero,
                         s, xc_hi, Nx.split && nrhs > 1 ? Nx.nf : -1,
@@ -913,6 +1076,22 @@ lair_status solve_fgmres_impl(lair_hierarchy *h, const double *b, double *x,
     return relmax <= rtol ? LAIR_OK : LAIR_ENOCONV;
 }
 
+// The union's vectors that the systems' tails read and write.
+static void set_batch_vectors(lair_hierarchy *h, bool mixed) {
+    for (size_t l = 0; l < h->L.size(); ++l) {
+        Level &Lv = *h->L[l];
+        if (mixed) {
+            auto &o = h->batch_tail->a32->lv[l];
+            o.vb = l ? Lv.b32.get() : h->r0_32.get();
+            o.vx = l ? Lv.x32.get() : h->e32.get();
+        } else {
+            auto &o = h->batch_tail->a64->lv[l];
+            o.vb = l ? Lv.b.get() : h->r0.get();
+            o.vx = l ? Lv.x.get() : h->e64.get();
+        }
+    }
+}
+
 // Batch of independent systems (one right-hand side each): the correction
 // form x += B (b - A x) on the union, with the residual rows of converged
 // systems zeroed so that their corrections vanish.  Each system stops at its
@@ -924,7 +1103,7 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     check_solve_args(h, b, x, rtol, maxit);
     if (!h->batch) fail(LAIR_EINVAL, "the hierarchy was not built by lair_setup_batch");
     ensure_vectors(h, 1, s);
-    ensure_tail(h, 1, h->opt.precision == LAIR_MIXED, false, s);
+    if (h->nsys == 1) ensure_tail(h, 1, h->opt.precision == LAIR_MIXED, false, s);
     Level &L0 = *h->L[0];
     const int32_t ns = h->nsys;
     const int64_t n = L0.n;
@@ -936,16 +1115,17 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     if (!mixed && h->e64.get() == nullptr) { h->e64.alloc((size_t)n, s); moved = true; }
     // one system: the iteration stops when it converges, no lists needed
     const bool lists = ns > 1;
-    const size_t cnt_bytes = (3 * sizeof(int32_t) * h->L.size() + 15) & ~(size_t)15;
+    const size_t cnt_bytes = (4 * sizeof(int32_t) * h->L.size() + 15) & ~(size_t)15;
     if (lists && L0.act_cnt == nullptr) {
-        const size_t maxseg = 3 * h->L.size() * (size_t)ns;
+        const size_t maxseg = 4 * h->L.size() * (size_t)ns;
         h->act_upload.alloc(cnt_bytes + sizeof(int64_t) * (maxseg + 1) +
                                 3 * sizeof(int32_t) * maxseg + 64, s);
         for (size_t l = 0; l < h->L.size(); ++l) {
             Level &Lv = *h->L[l];
-            Lv.act_cnt = reinterpret_cast<int32_t *>(h->act_upload.get()) + 3 * l;
+            Lv.act_cnt = reinterpret_cast<int32_t *>(h->act_upload.get()) + 4 * l;
             Lv.act_rows.alloc((size_t)std::max(Lv.n, 1), s);
             if (l + 1 < h->L.size()) {
+                Lv.act_p.alloc((size_t)std::max(Lv.n, 1), s);
                 Lv.act_f.alloc((size_t)std::max(Lv.nf, 1), s);
                 Lv.act_c.alloc((size_t)std::max(Lv.nrc >= 0 ? Lv.nrc : Lv.nc, 1), s);
             }
@@ -979,6 +1159,7 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
         moved = true;
     }
     if (moved) h->drop_graphs();
+    const size_t nlev = h->L.size();
     auto seg_norms = [&](const double *r, const uint8_t *act, hipStream_t st) {
         ProfScope ps("norm", st, 8.0 * n, 2.0 * n);
         launch_seg_sumsq_blocks(ns, h->ss_nblk, h->ss_sys.get(), h->ss_lo.get(),
@@ -989,7 +1170,6 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     // F rows and relaxed C rows are contiguous runs of the level's row range,
     // F list and relaxed-C list; the host lays out the runs of the active
     // systems and one kernel copies them (no atomics, fixed order).
-    const size_t nlev = h->L.size();
     std::vector<std::array<std::vector<int32_t>, 3>> runs(nlev);   // per list: prefix over systems
     for (size_t l = 0; lists && l < nlev; ++l) {
         Level &Lv = *h->L[l];
@@ -1007,49 +1187,66 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
             runs[l][2][q + 1] = runs[l][2][q] + rq;
         }
     }
+    // the systems' tails, one workgroup each
+    if (lists && !h->batch_tail) {
+        h->batch_tail = mixed ? make_batch_tail<float>(h, runs, s)
+                              : make_batch_tail<double>(h, runs, s);
+        if (!h->batch_tail) {
+            h->batch_tail.reset(new Tail());      // none: past every level
+            h->batch_tail->start = nlev;
+            h->batch_tail->top.assign((size_t)ns, (int32_t)nlev);
+        }
+        h->drop_graphs();
+    }
+    const std::vector<int32_t> no_top;
+    const std::vector<int32_t> &top = lists ? h->batch_tail->top : no_top;
     DevArr<const int32_t *> d_src;
     DevArr<int32_t *> d_dst;
     if (lists) {
-        std::vector<const int32_t *> srcs(3 * nlev, nullptr);
-        std::vector<int32_t *> dsts(3 * nlev, nullptr);
+        std::vector<const int32_t *> srcs(4 * nlev, nullptr);
+        std::vector<int32_t *> dsts(4 * nlev, nullptr);
         for (size_t l = 0; l < nlev; ++l) {
             Level &Lv = *h->L[l];
-            dsts[3 * l] = Lv.act_rows.get();
+            dsts[4 * l] = Lv.act_rows.get();
             if (l + 1 < nlev) {
-                srcs[3 * l + 1] = Lv.flist.get();
-                dsts[3 * l + 1] = Lv.act_f.get();
-                srcs[3 * l + 2] = Lv.nrc >= 0 ? Lv.rclist.get() : Lv.clist.get();
-                dsts[3 * l + 2] = Lv.act_c.get();
+                srcs[4 * l + 1] = Lv.flist.get();
+                dsts[4 * l + 1] = Lv.act_f.get();
+                srcs[4 * l + 2] = Lv.nrc >= 0 ? Lv.rclist.get() : Lv.clist.get();
+                dsts[4 * l + 2] = Lv.act_c.get();
+                dsts[4 * l + 3] = Lv.act_p.get();
             }
         }
-        d_src.alloc(3 * nlev, s);
-        d_dst.alloc(3 * nlev, s);
-        LAIR_HIP(hipMemcpyAsync(d_src.get(), srcs.data(), sizeof(void *) * 3 * nlev,
+        d_src.alloc(4 * nlev, s);
+        d_dst.alloc(4 * nlev, s);
+        LAIR_HIP(hipMemcpyAsync(d_src.get(), srcs.data(), sizeof(void *) * 4 * nlev,
                                 hipMemcpyHostToDevice, s));
-        LAIR_HIP(hipMemcpyAsync(d_dst.get(), dsts.data(), sizeof(void *) * 3 * nlev,
+        LAIR_HIP(hipMemcpyAsync(d_dst.get(), dsts.data(), sizeof(void *) * 4 * nlev,
                                 hipMemcpyHostToDevice, s));
         LAIR_HIP(hipStreamSynchronize(s));     // the pointer tables are pageable host memory
     }
     auto rebuild_lists = [&]() {
         std::vector<int64_t> out{0};
         std::vector<int32_t> src, dst, lst;
-        std::vector<int32_t> counts(3 * nlev, 0);
+        std::vector<int32_t> counts(4 * nlev, 0);
         for (size_t l = 0; l < nlev; ++l)
-            for (int t = 0; t < 3; ++t) {
+            for (int t = 0; t < 4; ++t) {
                 if (t > 0 && l + 1 == nlev) continue;
                 int32_t pos = 0;
                 for (int32_t q = 0; q < ns; ++q) {
-                    if (!h->active[q]) continue;
-                    const int32_t len = runs[l][t][q + 1] - runs[l][t][q];
+                    // a system's tail takes its right-hand side at level
+                    // top[q] and does the rest from there
+                    if (!h->active[q] || (size_t)top[q] + (t == 0) <= l) continue;
+                    const int k = t == 3 ? 0 : t;
+                    const int32_t len = runs[l][k][q + 1] - runs[l][k][q];
                     if (len == 0) continue;
-                    const int32_t start = t == 0 ? (int32_t)h->L[l]->seg[q] : runs[l][t][q];
+                    const int32_t start = k == 0 ? (int32_t)h->L[l]->seg[q] : runs[l][k][q];
                     out.push_back(out.back() + len);
                     src.push_back(start);
                     dst.push_back(pos);
-                    lst.push_back((int32_t)(3 * l + t));
+                    lst.push_back((int32_t)(4 * l + t));
                     pos += len;
                 }
-                counts[3 * l + t] = pos;
+                counts[4 * l + t] = pos;
             }
         const int32_t nseg = (int32_t)lst.size();
         // one pinned upload area with the device layout: the list lengths
@@ -1126,6 +1323,7 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
         // the cycle touches only the rows of systems still iterated; the
         // others keep their x (their corrections would be zero)
         h->use_act = lists;
+        if (lists && h->batch_tail->start < nlev) set_batch_vectors(h, mixed);
         run_iteration(h, mixed ? IT_BATCH_MIXED : IT_BATCH_FP64, 1, bb, x, s,
                       [&](hipStream_t st) {
             if (mixed) {

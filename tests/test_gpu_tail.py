@@ -106,3 +106,35 @@ def test_transposed_tail_against_oracle(lair, name, nrhs):
         ref = O.cycle_transpose(H, g[:, q], np.zeros(n), omega=omega)
         assert np.abs(lam[:, q] - ref).max() <= 1e-11 * np.abs(ref).max()
     h.free()
+
+
+# one cycle of a batch from zero is x = B b whichever way it runs: the batch
+# solve runs each system's small levels in a workgroup of its own, the cycle
+# call launches every level over the union.  Grids of 1 to 10,201 rows: a
+# system that is its coarsest grid, one whose largest level just fits a
+# workgroup (67^2 = 4,489 rows) and one that does not (68^2 = 4,624)
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("kw", [dict(interp="direct"), dict(distance=2, omega=0.9),
+                                dict(interp="direct", split="pmis", max_coarse=40),
+                                dict(split="pmis", lump_tol=1e-3)],
+                         ids=["direct", "distance2", "pmis", "pmis_lumped"])
+@pytest.mark.parametrize("sizes", [(1, 8, 11, 23), (67, 3, 68), (101, 12, 67, 40, 40, 31)],
+                         ids=["small", "edge", "uneven"])
+def test_batch_workgroups_equal_launches(lair, sizes, kw, precision):
+    import torch
+    print("case: batch tail", sizes, kw, precision, flush=True)
+    rng = np.random.default_rng(3)
+    systems = [W.adr_2d(m, 10.0 ** rng.uniform(-4, -1), rng.uniform(0, 6), rng.uniform(0, 1))
+               for m in sizes]
+    h = lair.setup_batch([(w["rowptr"], w["col"], w["val"]) for w in systems],
+                         precision=precision, **kw)
+    b = torch.as_tensor(rng.standard_normal(h.n), device="cuda")
+    launched = h.cycle(b, torch.zeros_like(b))
+    lair.profile_begin(["tail"])
+    x, info = h.solve_batch(b, maxit=1)
+    prof = lair.profile_end()
+    assert prof["tail"]["launches"] == 1
+    assert torch.isfinite(x).all() and torch.equal(launched, x)
+    again, _ = h.solve_batch(b, maxit=1)          # captured iterations
+    assert torch.equal(x, again)
+    h.free()
