@@ -123,10 +123,10 @@ typedef struct lair_options {
                                 use 0.001)                                 */
 } lair_options;
 
-/* Solves capture one iteration (cycle, residual, norms) in a HIP graph the
- * first time a (b, x, nrhs) combination is seen, on a private stream of
- * default priority, and replay it on the caller's stream afterwards; the
- * results are bitwise those of eager launches.  This flag launches every
+/* Solves capture an iteration (cycle, residual, norms) in a HIP graph once a
+ * (b, x, nrhs) combination has run a few tens of iterations, on a private
+ * stream of default priority, and replay it on the caller's stream afterwards;
+ * the results are bitwise those of eager launches.  This flag launches every
  * kernel eagerly instead.  Iterations are also eager while the profiler
  * times a cycle category. */
 #define LAIR_FLAG_NO_GRAPH 1

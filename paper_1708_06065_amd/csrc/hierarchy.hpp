@@ -23,7 +23,10 @@ namespace lair {
 // ---------------------------------------------------------------------------
 struct Level {
     DevCSR A, R, P;            // A_l (n x n), R_l (nc x n), P_l (n x nc)
-    DevCSR At, Rt, Pt;         // transposes for the adjoint cycle
+    DevCSR At, Rt, Pt;         // transposes for the adjoint cycle, and where
+    DevArr<int32_t> At_pos, Rt_pos, Pt_pos;   // their entries lie in A, R and P
+    DevArr<double> tdiag;      // A's diagonal
+    DevArr<int8_t> tkind;      // 1 at the relaxed C rows
     int32_t n = 0, nc = 0, nf = 0;
     int64_t nnzF = 0, nnzC = 0;     // stored entries in the F rows / C rows
     DevArr<unsigned long long> fc_acc;   // their device sums until read at the end of setup
@@ -82,6 +85,9 @@ struct Tail {
     DevArr<char> blob;
     std::unique_ptr<TailArgs<double>> a64;
     std::unique_ptr<TailArgs<float>> a32;
+    std::vector<TailSources<double>> src64;    // per level, for new values
+    std::vector<TailSources<float>> src32;
+    bool stale = false;                        // packed from old values
     double bytes = 0.0, flops = 0.0;   // algorithmic, of its levels
     // batch: the level each system's tail starts at; `start` is the last of
     // them, where the tail is launched
@@ -109,6 +115,7 @@ struct lair_hierarchy {
     lair::DevArr<double> bscaled, r0, partial, norms;
     lair::DevArr<float> r0_32, e32;
     bool have_transpose = false;
+    bool transpose_stale = false;            // kept patterns, old values
     // batch of independent systems (nsys > 1): per-system coarsest blocks
     int32_t nsys = 1;
     lair::DevArr<int64_t> dense_off;
@@ -139,14 +146,16 @@ struct lair_hierarchy {
     // captured solve iterations (cycle + residual + norms), keyed by the
     // iteration kind, the number of right-hand sides and the caller's b and
     // x; captured on a private stream, replayed on the caller's stream
-    struct Graph { int kind; int32_t nrhs; const void *b; void *x; hipGraphExec_t exec; };
+    // (runs: iterations launched before that; exec null until then)
+    struct Graph { int kind; int32_t nrhs; const void *b; void *x; int runs; hipGraphExec_t exec; };
     std::vector<Graph> graphs;
     hipStream_t gstream = nullptr;
     void drop_graphs() {
-        for (auto &g : graphs) (void)hipGraphExecDestroy(g.exec);
+        for (auto &g : graphs)
+            if (g.exec) (void)hipGraphExecDestroy(g.exec);
         graphs.clear();
     }
-    // packed tails, made when a cycle first asks for one (new values: cleared)
+    // packed tails, made when a cycle first asks for one
     std::vector<lair::Tail> tails;
     std::unique_ptr<lair::Tail> batch_tail;  // of a batch solve
     ~lair_hierarchy() {
@@ -216,8 +225,9 @@ inline VT *vec(DevArr<double> &d, DevArr<float> &f) {
 void rs_first_pass(int64_t n, const int32_t *rp, const int32_t *cj,
                    const uint8_t *sm, int8_t *cf);
 void check_options(const lair_strength *s, const lair_options *o);
-// T = M^T (CSR), with the team sizes of its rows
-void transpose(const DevCSR &M, DevCSR &T, hipStream_t s, DevArr<int64_t> &tmp);
+// T = M^T (CSR); pos: where T's entries lie in M
+void transpose(const DevCSR &M, DevCSR &T, DevArr<int32_t> &pos, hipStream_t s,
+               DevArr<int64_t> &tmp);
 lair_hierarchy *setup_impl(const lair_csr *Ain, const lair_cf_levels *cfl,
                            const lair_strength *str, const lair_options *opt,
                            hipStream_t s, const std::vector<int64_t> *seg = nullptr);

@@ -784,6 +784,40 @@ void op_copy(const VT *x, VT *y, int64_t n, hipStream_t s) {
     LAIR_LAUNCH_CHECK();
 }
 
+// The same expressions as the sweep kernels, whose product with a zero iterate
+// is zero: one launch where a fill, a sweep and a scatter were three.
+__global__ void __launch_bounds__(256)
+k_first_sweep(int64_t total, int32_t nrhs, const int8_t *kind, const double *g, const double *d,
+              double omega, double *x, double *y) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= total) return;
+    const int64_t i = e / nrhs;
+    double v = 0.0;
+    if (kind[i] == 1) v = 0.0 + omega * (g[e] - 0.0) / d[i];
+    x[e] = v;
+    y[e] = v;
+}
+
+void op_first_sweep(int64_t n, int32_t nrhs, const int8_t *kind, const double *g,
+                    const double *d, double omega, double *x, double *y, hipStream_t s) {
+    if (n == 0) return;
+    LAIR_LAUNCH(k_first_sweep, dim3(blocks_for(n * nrhs, 256)), dim3(256), 0, s, n * nrhs, nrhs,
+                kind, g, d, omega, x, y);
+    LAIR_LAUNCH_CHECK();
+}
+
+__global__ void k_row_kind(int32_t m, const int32_t *rows, int8_t *kind) {
+    const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < m) kind[rows[k]] = 1;
+}
+
+void launch_row_kind(int32_t n, const int32_t *rows, int32_t m, int8_t *kind, hipStream_t s) {
+    LAIR_HIP(hipMemsetAsync(kind, 0, (size_t)std::max(n, 1), s));
+    if (m == 0) return;
+    LAIR_LAUNCH(k_row_kind, dim3(blocks_for(m, 256)), dim3(256), 0, s, m, rows, kind);
+    LAIR_LAUNCH_CHECK();
+}
+
 // ---------------------------------------------------------------------------
 // Coarsest grid: x = K^{-1} b (or K^{-T} b) from P K = L U, one block,
 // right-hand sides in parallel.

@@ -367,10 +367,23 @@ void launch_spgemm(int32_t m, const int32_t *ap, const int32_t *aj, const double
 void launch_spgemm_compact(int32_t m, const int64_t *eoff, const int32_t *crp,
                            const int32_t *tcj, const double *tcx, int32_t *cj, double *cx,
                            double mean_c, hipStream_t s);
+// T = M^T (trp: ncols + 1); tpos: where each entry of T lies in M
 void launch_transpose(int32_t nrows, int32_t ncols, int64_t nnz,
                       const int32_t *rp, const int32_t *cj, const double *v,
-                      int32_t *tcount, int32_t *trp, int32_t *tcj, double *tv,
-                      int32_t *cursor, hipStream_t s, DevArr<int64_t> &tmp);
+                      int32_t *trp, int32_t *tcj, int32_t *tpos, double *tv, hipStream_t s,
+                      DevArr<int64_t> &tmp);
+// tv[k] = v[pos[k]] for several matrices (a kernel argument: 4 KB)
+struct TransposeValues {
+    struct One {
+        const double *v;
+        const int32_t *pos;
+        double *tv;
+        int64_t nnz;
+    } m[96];
+};
+void launch_transpose_values(const TransposeValues &t, int count, hipStream_t s);
+void launch_diagonal(int32_t n, const int32_t *rp, const int32_t *cj, const double *v, double *d,
+                     hipStream_t s);
 void launch_to_float(const double *in, float *out, int64_t n, hipStream_t s);
 void launch_block_inverse(int32_t nblk, int32_t k, const int32_t *rp,
                           const int32_t *cj, const double *v, double *dinv,
@@ -441,6 +454,12 @@ template <class VT>
 void op_fill(VT *x, VT val, int64_t n, hipStream_t s);
 template <class VT>
 void op_copy(const VT *x, VT *y, int64_t n, hipStream_t s);
+// The first sweep of a transposed cycle, on the C rows (kind[i] = 1) of a
+// zero iterate: x_i = y_i = omega g_i / d_i there and 0 elsewhere.
+void op_first_sweep(int64_t n, int32_t nrhs, const int8_t *kind, const double *g,
+                    const double *d, double omega, double *x, double *y, hipStream_t s);
+// kind[i] = 1 for the listed rows and 0 elsewhere
+void launch_row_kind(int32_t n, const int32_t *rows, int32_t m, int8_t *kind, hipStream_t s);
 template <class VT>
 void op_dense_solve(int32_t n, const double *lu, const int32_t *piv,
                     const VT *b, VT *x, int32_t nrhs, bool transpose,

@@ -372,22 +372,18 @@ static int32_t spgemm(const DevCSR &A, int32_t max_row_a, const DevCSR &B,
                          c_nnz > 0 ? (double)st.h[0] / (double)c_nnz : 0.0);
 }
 
-void transpose(const DevCSR &M, DevCSR &T, hipStream_t s, DevArr<int64_t> &tmp) {
+void transpose(const DevCSR &M, DevCSR &T, DevArr<int32_t> &pos, hipStream_t s,
+               DevArr<int64_t> &tmp) {
     T.nrows = M.ncols;
     T.ncols = M.nrows;
     T.nnz = M.nnz;
-    DevArr<int32_t> cnt, cur;
-    cnt.alloc((size_t)M.ncols + 1, s);
-    cur.alloc((size_t)M.ncols + 1, s);
+    const size_t z = (size_t)std::max<int64_t>(M.nnz, 1);
     T.rp.alloc((size_t)M.ncols + 1, s);
-    T.cj.alloc((size_t)std::max<int64_t>(M.nnz, 1), s);
-    T.v.alloc((size_t)std::max<int64_t>(M.nnz, 1), s);
+    T.cj.alloc(z, s);
+    T.v.alloc(z, s);
+    pos.alloc(z, s);
     launch_transpose(M.nrows, M.ncols, M.nnz, M.rp.get(), M.cj.get(), M.v.get(),
-                     cnt.get(), T.rp.get(), T.cj.get(), T.v.get(), cur.get(), s, tmp);
-    if (M.v32.get()) {
-        T.v32.alloc((size_t)std::max<int64_t>(M.nnz, 1), s);
-        launch_to_float(T.v.get(), T.v32.get(), T.nnz, s);
-    }
+                     T.rp.get(), T.cj.get(), pos.get(), T.v.get(), s, tmp);
 }
 
 void check_options(const lair_strength *s, const lair_options *o) {
@@ -811,11 +807,11 @@ static void finish_coarsest_batch(lair_hierarchy *h) {
     ProfScope ps("coarse_setup", s, 8.0 * (double)doff[ns], 0.0);
     h->nL = Lc.n;
     h->coarse_entries = (double)doff[ns];
-    h->dense_off.alloc((size_t)ns + 1, s);
+    h->dense_off.ensure((size_t)ns + 1, s);
     LAIR_HIP(hipMemcpyAsync(h->dense_off.get(), doff.data(), sizeof(int64_t) * (ns + 1),
                             hipMemcpyHostToDevice, s));
-    h->lu.alloc((size_t)std::max<int64_t>(doff[ns], 1), s);
-    h->piv.alloc((size_t)std::max(Lc.n, 1), s);
+    h->lu.ensure((size_t)std::max<int64_t>(doff[ns], 1), s);
+    h->piv.ensure((size_t)std::max(Lc.n, 1), s);
     DevArr<int32_t> info;
     info.alloc(1, s);
     LAIR_HIP(hipMemsetAsync(info.get(), 0, sizeof(int32_t), s));
@@ -837,9 +833,9 @@ static void finish_coarsest_batch(lair_hierarchy *h) {
         }
         mmax = std::max(mmax, m);
     }
-    h->use_inv.alloc((size_t)ns, s);
+    h->use_inv.ensure((size_t)ns, s);
     LAIR_HIP(hipMemcpyAsync(h->use_inv.get(), ui.data(), (size_t)ns, hipMemcpyHostToDevice, s));
-    if (any) h->binv.alloc((size_t)std::max<int64_t>(doff[ns], 1), s);
+    if (any) h->binv.ensure((size_t)std::max<int64_t>(doff[ns], 1), s);
     else h->binv.release();
     launch_block_lu_inv_small(ns, Lc.seg_dev.get(), h->dense_off.get(), h->lu.get(),
                               h->piv.get(), h->binv.get(), info.get(), s);
@@ -874,13 +870,13 @@ static void finish_coarsest(lair_hierarchy *h) {
     ProfScope ps("coarse_setup", s, 8.0 * n * (double)n, 2.0 / 3.0 * n * (double)n * n);
     h->nL = n;
     h->coarse_entries = (double)n * (double)n;
-    h->lu.alloc((size_t)n * n, s);
-    h->piv.alloc((size_t)std::max(n, 1), s);
+    h->lu.ensure((size_t)n * n, s);
+    h->piv.ensure((size_t)std::max(n, 1), s);
     DevArr<int32_t> info;
     info.alloc(1, s);
     launch_dense_from_csr(n, Lc.A.rp.get(), Lc.A.cj.get(), Lc.A.v.get(), h->lu.get(), s);
     bool have_inv = false;
-    if (n <= MAX_INVERSE) h->kinv.alloc((size_t)n * n, s);
+    if (n <= MAX_INVERSE) h->kinv.ensure((size_t)n * n, s);
     // small grids: the inverse directly, in one workgroup (the cycle only
     // applies the inverse; no factors are kept)
     if (n <= MAX_INVERSE && launch_dense_gj_inv(n, h->lu.get(), h->kinv.get(), info.get(), s))
@@ -975,10 +971,10 @@ struct SplitCopies {
         Level &Lv = *h->L[l];
         if (!Lv.split) return;
         const size_t n = (size_t)std::max(Lv.n, 1);
-        Lv.perm.alloc(n, s);
-        Lv.iperm.alloc(n, s);
-        Lv.ids.alloc(n, s);
-        Lv.cf_split.alloc(n, s);
+        Lv.perm.ensure(n, s);
+        Lv.iperm.ensure(n, s);
+        Lv.ids.ensure(n, s);
+        Lv.cf_split.ensure(n, s);
         launch_split_perm(Lv.nf, Lv.nc, Lv.flist.get(), Lv.clist.get(), Lv.perm.get(),
                           Lv.iperm.get(), Lv.ids.get(), Lv.cf_split.get(), s);
     }
@@ -989,11 +985,11 @@ struct SplitCopies {
         O.nnz = M.nnz;
         O.max_row = M.max_row;
         const size_t z = (size_t)std::max<int64_t>(M.nnz, 1);
-        O.rp.alloc((size_t)M.nrows + 1, s);
-        O.cj.alloc(z, s);
-        if (!mixed) O.v.alloc(z, s); else O.v.release();
-        if (mixed) O.v32.alloc(z, s); else O.v32.release();
-        if (cjt) cjt->alloc(z, s);
+        O.rp.ensure((size_t)M.nrows + 1, s);
+        O.cj.ensure(z, s);
+        if (!mixed) O.v.ensure(z, s); else O.v.release();
+        if (mixed) O.v32.ensure(z, s); else O.v32.release();
+        if (cjt) cjt->ensure(z, s);
         launch_permute_csr(M.nrows, M.nnz, M.nrows ? (double)M.nnz / M.nrows : 0.0, rowmap,
                            irowmap, colmap, M.rp.get(), M.cj.get(), M.v.get(), O.rp.get(),
                            O.cj.get(),
@@ -1440,11 +1436,24 @@ void update_diag_impl(lair_hierarchy *h, const double *diag, int32_t on_device,
     LAIR_LAUNCH(k_set_diag, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, L0.A.rp.get(),
                 L0.A.cj.get(), L0.A.v.get(), dd);
     LAIR_LAUNCH_CHECK();
-    h->drop_graphs();
-    h->tails.clear();
-    h->batch_tail.reset();
-    h->have_transpose = false;
+    // every array keeps its place (the patterns are kept), so captured
+    // iterations stay valid; packed and transposed values are made again when
+    // they are next asked for
+    h->transpose_stale = true;
+    for (auto &t : h->tails) t.stale = true;
+    if (h->batch_tail) h->batch_tail->stale = true;
     h->n_singular = 0;
+    // what a failed update leaves may not be used again
+    struct Failed {
+        lair_hierarchy *h;
+        bool done = false;
+        ~Failed() {
+            if (done) return;
+            h->drop_graphs();
+            h->tails.clear();
+            h->batch_tail.reset();
+        }
+    } failed{h};
     DevArr<int64_t> tmp;
     const int32_t prec = h->opt.precision == LAIR_FP64 ? LAIR_FP64 : LAIR_MIXED;
     for (size_t l = 0; l + 1 < h->L.size(); ++l) {
@@ -1470,13 +1479,16 @@ void update_diag_impl(lair_hierarchy *h, const double *diag, int32_t on_device,
         Level &Nx = *h->L[l + 1];
         if (K.nnz != Nx.A.nnz)
             fail(LAIR_EDEVICE, "coarse operator pattern changed on update (level %zu)", l + 1);
-        Nx.A = std::move(K);
-        Nx.max_row = mr;
+        if (K.nnz > 0)
+            LAIR_HIP(hipMemcpyAsync(Nx.A.v.get(), K.v.get(), sizeof(double) * (size_t)K.nnz,
+                                    hipMemcpyDeviceToDevice, s));
+        (void)mr;
     }
     finish_coarsest(h);
     finish_cycle_operators(h, s);
     level_stats_and_cc(h);
     LAIR_HIP(hipStreamSynchronize(s));
+    failed.done = true;
 }
 
 // Union of a batch: the systems' matrices placed block-diagonally, rows of

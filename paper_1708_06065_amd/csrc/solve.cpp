@@ -222,6 +222,25 @@ static std::unique_ptr<TailArgs<VT>> &tail_args(Tail &t) {
     else return t.a32;
 }
 
+template <class VT>
+static std::vector<TailSources<VT>> &tail_sources(Tail &t) {
+    if constexpr (std::is_same<VT, double>::value) return t.src64;
+    else return t.src32;
+}
+
+// Pack every level (again, when the operators have new values).
+template <class VT>
+static void pack_tail(Tail &t, hipStream_t s) {
+    for (auto &src : tail_sources<VT>(t)) launch_tail_pack<VT>(src, s);
+    t.stale = false;
+}
+
+static void repack(Tail &t, hipStream_t s) {
+    if (!t.stale) return;
+    if (t.w == 4) pack_tail<float>(t, s);
+    else pack_tail<double>(t, s);
+}
+
 // Pack the tail's operators for nrhs right-hand sides (on s).
 template <class VT>
 static Tail make_tail(lair_hierarchy *h, size_t start, int32_t nrhs, bool transpose,
@@ -258,7 +277,8 @@ static Tail make_tail(lair_hierarchy *h, size_t start, int32_t nrhs, bool transp
         }
         max_rows((int)rp.size(), rp.data(), n.data(), longest.data(), s);
     }
-    std::vector<TailSources<VT>> src((size_t)nlv);
+    auto &src = tail_sources<VT>(T);
+    src.resize((size_t)nlv);
     size_t total = 0;
     for (int32_t k = 0; k < nlv; ++k) {
         Level &Lv = *h->L[start + k];
@@ -317,30 +337,37 @@ static Tail make_tail(lair_hierarchy *h, size_t start, int32_t nrhs, bool transp
     for (int32_t k = 0; k + 1 < nlv; ++k) {
         src[k].blob = T.blob.get();
         for (int t = 0; t < TAIL_SETS; ++t) a->lv[k].set[t] = src[k].src[t].dst;
-        launch_tail_pack<VT>(src[k], s);
     }
+    pack_tail<VT>(T, s);
     return T;
 }
 
-// The tail a cycle of this kind uses from level l on, or nullptr.
+// The tail a cycle of this kind uses from level l on, or nullptr (one packed
+// from old values is not used).
 template <class VT>
 static Tail *find_tail(lair_hierarchy *h, int32_t nrhs, bool transpose, size_t l) {
     for (auto &t : h->tails)
         if (t.w == (int)sizeof(VT) && t.nrhs == nrhs && t.transpose == transpose)
-            return l >= t.start && tail_args<VT>(t) ? &t : nullptr;
+            return l >= t.start && tail_args<VT>(t) && !t.stale ? &t : nullptr;
     return nullptr;
 }
 
-// Make the tail of a cycle kind if there is none yet.  Not while the stream
-// is captured: the cycle then runs launch by launch, the same sums.
+// Make the tail of a cycle kind, or pack it again after new values.  Not while
+// the stream is captured: the cycle then runs launch by launch, the same sums.
 static void ensure_tail(lair_hierarchy *h, int32_t nrhs, bool mixed, bool transpose,
                         hipStream_t s) {
     const int w = mixed ? 4 : 8;
+    Tail *have = nullptr;
     for (auto &t : h->tails)
-        if (t.w == w && t.nrhs == nrhs && t.transpose == transpose) return;
+        if (t.w == w && t.nrhs == nrhs && t.transpose == transpose) have = &t;
+    if (have && !have->stale) return;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
+        return;
+    }
+    if (have) {
+        repack(*have, s);
         return;
     }
     const size_t start = tail_start(h, w, transpose);
@@ -432,7 +459,8 @@ static std::unique_ptr<Tail> make_batch_tail(lair_hierarchy *h,
     a->slev = d + 2 * ns;
     T->bytes = 8.0 * h->coarse_entries + 2.0 * w * h->nL;
     T->flops = 2.0 * h->coarse_entries;
-    std::vector<TailSources<VT>> src((size_t)nl);
+    auto &src = tail_sources<VT>(*T);
+    src.resize((size_t)nl);
     size_t total = 0;
     for (int32_t l = 0; l < nl; ++l) {
         Level &Lv = *h->L[l];
@@ -505,8 +533,8 @@ static std::unique_ptr<Tail> make_batch_tail(lair_hierarchy *h,
     for (int32_t l = 0; l + 1 < nl; ++l) {
         src[l].blob = T->blob.get();
         for (int t = 0; t < TAIL_A; ++t) a->lv[l].set[t] = src[l].src[t].dst;
-        launch_tail_pack<VT>(src[l], s);
     }
+    pack_tail<VT>(*T, s);
     LAIR_HIP(hipStreamSynchronize(s));     // the staging area is reused
     return T;
 }
@@ -581,51 +609,79 @@ static const VT *vcycle(lair_hierarchy *h, size_t l, const VT *b, VT *x, bool x_
 
 // Transposed cycle: C, F, F Jacobi on A^T, restriction with P^T, recursion
 // on K^T, interpolation with R^T.
-static void ensure_transposes(lair_hierarchy *h) {
-    if (h->have_transpose) return;
+static void ensure_transposes(lair_hierarchy *h, hipStream_t cs) {
+    if (h->have_transpose && !h->transpose_stale) return;
+    const size_t nl = h->L.size();
+    if (h->have_transpose) {
+        // new values on the kept patterns
+        TransposeValues t{};
+        int m = 0;
+        auto add = [&](const DevCSR &M, DevCSR &T, const DevArr<int32_t> &pos) {
+            t.m[m++] = {M.v.get(), pos.get(), T.v.get(), M.nnz};
+            if (m == 96) {
+                launch_transpose_values(t, m, cs);
+                m = 0;
+            }
+        };
+        for (size_t l = 0; l < nl; ++l) {
+            Level &Lv = *h->L[l];
+            add(Lv.A, Lv.At, Lv.At_pos);
+            if (l + 1 == nl) break;
+            add(Lv.R, Lv.Rt, Lv.Rt_pos);
+            add(Lv.P, Lv.Pt, Lv.Pt_pos);
+            launch_diagonal(Lv.n, Lv.A.rp.get(), Lv.A.cj.get(), Lv.A.v.get(), Lv.tdiag.get(), cs);
+        }
+        if (m) launch_transpose_values(t, m, cs);
+        h->transpose_stale = false;
+        return;
+    }
     hipStream_t s = h->stream;
     DevArr<int64_t> tmp;
-    for (size_t l = 0; l < h->L.size(); ++l) {
+    for (size_t l = 0; l < nl; ++l) {
         Level &Lv = *h->L[l];
-        transpose(Lv.A, Lv.At, s, tmp);
+        transpose(Lv.A, Lv.At, Lv.At_pos, s, tmp);
         Lv.team_At = team_of(Lv.At);
-        if (l + 1 == h->L.size()) break;
-        transpose(Lv.R, Lv.Rt, s, tmp);
-        transpose(Lv.P, Lv.Pt, s, tmp);
+        if (l + 1 == nl) break;
+        transpose(Lv.R, Lv.Rt, Lv.Rt_pos, s, tmp);
+        transpose(Lv.P, Lv.Pt, Lv.Pt_pos, s, tmp);
         Lv.team_Rt = team_of(Lv.Rt);
         Lv.team_Pt = team_of(Lv.Pt);
+        Lv.tdiag.alloc((size_t)std::max(Lv.n, 1), s);
+        launch_diagonal(Lv.n, Lv.A.rp.get(), Lv.A.cj.get(), Lv.A.v.get(), Lv.tdiag.get(), s);
+        Lv.tkind.alloc((size_t)std::max(Lv.n, 1), s);
+        launch_row_kind(Lv.n, Lv.nrc >= 0 ? Lv.rclist.get() : Lv.clist.get(),
+                        Lv.nrc >= 0 ? Lv.nrc : Lv.nc, Lv.tkind.get(), s);
     }
     LAIR_HIP(hipStreamSynchronize(s));
     h->have_transpose = true;
+    h->transpose_stale = false;
 }
 
-static void vcycle_t(lair_hierarchy *h, size_t l, const double *g, double *lam,
-                     bool lam_zero, int32_t nrhs, hipStream_t s) {
+// lam = B^T g from zero.  The C sweep of a zero iterate writes lam and the
+// work vector t; the first F sweep reads lam and writes t's F rows, the second
+// reads t and writes lam's.
+static void vcycle_t(lair_hierarchy *h, size_t l, const double *g, double *lam, int32_t nrhs,
+                     hipStream_t s) {
     Level &Lv = *h->L[l];
     if (l + 1 == h->L.size()) {
         coarse_solve<double>(h, g, lam, nrhs, true, s);
         return;
     }
-    if (Tail *T = lam_zero ? find_tail<double>(h, nrhs, true, l) : nullptr) {
+    if (Tail *T = find_tail<double>(h, nrhs, true, l)) {
         ProfScope ps("tail", s, T->bytes, T->flops);
         launch_tail_t(*T->a64, g, lam, s);
         return;
     }
-    if (lam_zero) op_fill<double>(lam, 0.0, (int64_t)Lv.n * nrhs, s);
     CsrView<double> At = view<double>(Lv.At, Lv.team_At);
-    double om = h->opt.omega;
-    const int32_t *crows = Lv.nrc >= 0 ? Lv.rclist.get() : Lv.clist.get();
-    const int32_t ncr = Lv.nrc >= 0 ? Lv.nrc : Lv.nc;
-    for (int sweep = 0; sweep < 3; ++sweep) {
-        const int32_t *rows = sweep == 0 ? crows : Lv.flist.get();
-        int32_t nx = sweep == 0 ? ncr : Lv.nf;
-        op_jacobi<double>(At, rows, nx, g, lam, lam, nullptr, Lv.t.get(), true, om, nrhs, s);
-        op_scatter<double>(rows, nx, Lv.t.get(), lam, nrhs, s);
-    }
+    const double om = h->opt.omega;
+    double *t = Lv.t.get();
+    op_first_sweep(Lv.n, nrhs, Lv.tkind.get(), g, Lv.tdiag.get(), om, lam, t, s);
+    op_jacobi<double>(At, Lv.flist.get(), Lv.nf, g, lam, lam, nullptr, t, false, om, nrhs, s);
+    op_jacobi<double>(At, Lv.flist.get(), Lv.nf, g, t, t, nullptr, lam, false, om, nrhs, s);
     op_residual<double>(At, g, lam, Lv.r.get(), nrhs, s);
     Level &Nx = *h->L[l + 1];
     op_spmv<double>(view<double>(Lv.Pt, Lv.team_Pt), Lv.r.get(), Nx.b.get(), nrhs, false, s);
-    vcycle_t(h, l + 1, Nx.b.get(), Nx.x.get(), true, nrhs, s);
+    vcycle_t(h, l + 1, Nx.b.get(), Nx.x.get(), nrhs, s);
     op_spmv<double>(view<double>(Lv.Rt, Lv.team_Rt), Nx.x.get(), lam, nrhs, true, s);
 }
 
@@ -662,7 +718,7 @@ static void norms_host(lair_hierarchy *h, const double *r, int32_t nrhs,
 }
 
 // Kinds of captured iterations.
-enum { IT_FP64 = 0, IT_MIXED = 1, IT_BATCH_FP64 = 2, IT_BATCH_MIXED = 3 };
+enum { IT_FP64 = 0, IT_MIXED = 1, IT_BATCH_FP64 = 2, IT_BATCH_MIXED = 3, IT_TRANSPOSE = 4 };
 
 static const char *const CYCLE_CATEGORIES[] = {
     "jacobi", "scatter", "residual", "restrict", "interpolate", "coarse_solve", "norm", "cast",
@@ -680,12 +736,18 @@ static bool use_graphs(const lair_hierarchy *h) {
 
 static const size_t MAX_GRAPHS = 8;
 
-// Run body(stream) on s: replay its captured graph.  The first iteration of
-// a kind is launched directly on s and then captured on the hierarchy's
-// private stream, so that the capture and the instantiation (host work of
-// a few hundred microseconds for a deep cycle) run while the device executes
-// that first iteration; later ones replay the graph.  body must launch
-// kernels only (no allocation, no host synchronisation, no memset).
+// Iterations of a kind launched before it is captured.  Capturing and
+// instantiating costs the host 0.1 to 0.4 ms, a replay saves a few
+// microseconds over launching what the tail leaves of a cycle (97 x 97, 17
+// iterations: 1.91 ms captured at once, 1.83 launched, 1.53 replayed; 80^3,
+// 10 iterations: 3.39, 3.23, 2.93), so a graph pays for combinations that
+// keep coming back.
+static const int GRAPH_AFTER = 24;
+
+// Run body(stream) on s.  The first iterations of a kind are launched
+// directly; then one is captured on the hierarchy's private stream, and later
+// ones replay its graph.  body must launch kernels only (no allocation, no
+// host synchronisation, no memset).
 template <class Body>
 static void run_iteration(lair_hierarchy *h, int kind, int32_t nrhs, const void *b, void *x,
                           hipStream_t s, Body &&body) {
@@ -693,12 +755,23 @@ static void run_iteration(lair_hierarchy *h, int kind, int32_t nrhs, const void 
         body(s);
         return;
     }
-    for (auto &g : h->graphs)
-        if (g.kind == kind && g.nrhs == nrhs && g.b == b && g.x == x) {
-            LAIR_HIP(hipGraphLaunch(g.exec, s));
-            return;
+    lair_hierarchy::Graph *g = nullptr;
+    for (auto &k : h->graphs)
+        if (k.kind == kind && k.nrhs == nrhs && k.b == b && k.x == x) g = &k;
+    if (!g) {
+        if (h->graphs.size() >= MAX_GRAPHS) {
+            if (h->graphs.front().exec) (void)hipGraphExecDestroy(h->graphs.front().exec);
+            h->graphs.erase(h->graphs.begin());
         }
+        h->graphs.push_back({kind, nrhs, b, x, 0, nullptr});
+        g = &h->graphs.back();
+    }
+    if (g->exec) {
+        LAIR_HIP(hipGraphLaunch(g->exec, s));
+        return;
+    }
     body(s);
+    if (++g->runs < GRAPH_AFTER) return;
     if (!h->gstream) LAIR_HIP(hipStreamCreateWithFlags(&h->gstream, hipStreamNonBlocking));
     hipGraph_t graph = nullptr;
     LAIR_HIP(hipStreamBeginCapture(h->gstream, hipStreamCaptureModeThreadLocal));
@@ -714,11 +787,7 @@ static void run_iteration(lair_hierarchy *h, int kind, int32_t nrhs, const void 
     hipError_t e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
     if (e != hipSuccess) fail(LAIR_EDEVICE, "graph instantiation failed: %s", hipGetErrorString(e));
-    if (h->graphs.size() >= MAX_GRAPHS) {
-        (void)hipGraphExecDestroy(h->graphs.front().exec);
-        h->graphs.erase(h->graphs.begin());
-    }
-    h->graphs.push_back({kind, nrhs, b, x, exec});
+    g->exec = exec;
 }
 
 static void check_solve_args(lair_hierarchy *h, const double *b, double *x, double rtol,
@@ -755,7 +824,7 @@ lair_status solve_impl(lair_hierarchy *h, const double *b, double *x,
     check_solve_args(h, b, x, rtol, maxit);
     check_nrhs(h, nrhs);
     ensure_vectors(h, nrhs, s);
-    if (transpose) ensure_transposes(h);
+    if (transpose) ensure_transposes(h, s);
     ensure_tail(h, nrhs, h->opt.precision == LAIR_MIXED && !transpose, transpose, s);
     Level &L0 = *h->L[0];
     const int64_t n = L0.n;
@@ -822,12 +891,13 @@ lair_status solve_impl(lair_hierarchy *h, const double *b, double *x,
         if (done || it >= maxit) break;
         if (transpose) {
             // lambda <- lambda + B^T (g - A^T lambda): cycle on the residual
-            DevArr<double> &e = L0.b;
-            vcycle_t(h, 0, h->r0.get(), e.get(), true, nrhs, s);
-            LAIR_LAUNCH(k_add, dim3(blocks_for(n * nrhs, 256)), dim3(256), 0, s,
-                               x, e.get(), n * nrhs);
-            LAIR_LAUNCH_CHECK();
-            residual_and_norms(s);
+            run_iteration(h, IT_TRANSPOSE, nrhs, bb, x, s, [&](hipStream_t st) {
+                vcycle_t(h, 0, h->r0.get(), L0.b.get(), nrhs, st);
+                LAIR_LAUNCH(k_add, dim3(blocks_for(n * nrhs, 256)), dim3(256), 0, st, x,
+                            L0.b.get(), n * nrhs);
+                LAIR_LAUNCH_CHECK();
+                residual_and_norms(st);
+            });
         } else if (!mixed) {
             run_iteration(h, IT_FP64, nrhs, bb, x, s, [&](hipStream_t st) {
                 vcycle<double>(h, 0, bb, x, false, h->r0.get(), nrhs, st);
@@ -1198,6 +1268,7 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
         }
         h->drop_graphs();
     }
+    if (lists) repack(*h->batch_tail, s);
     const std::vector<int32_t> no_top;
     const std::vector<int32_t> &top = lists ? h->batch_tail->top : no_top;
     DevArr<const int32_t *> d_src;
@@ -1433,13 +1504,13 @@ void cycle_transpose_impl(lair_hierarchy *h, const double *g, double *lam, int32
     check_nrhs(h, nrhs);
     if (nodal(h->opt)) fail(LAIR_EUNSUPPORTED, "transposed cycle on a nodal hierarchy");
     ensure_vectors(h, nrhs, s);
-    ensure_transposes(h);
+    ensure_transposes(h, s);
     ensure_tail(h, nrhs, false, true, s);
     // lam <- lam + B^T (g - A^T lam)
     Level &L0 = *h->L[0];
     int64_t n = L0.n;
     op_residual<double>(view<double>(L0.At, L0.team_At), g, lam, h->r0.get(), nrhs, s);
-    vcycle_t(h, 0, h->r0.get(), L0.b.get(), true, nrhs, s);
+    vcycle_t(h, 0, h->r0.get(), L0.b.get(), nrhs, s);
     LAIR_LAUNCH(k_add, dim3(blocks_for(n * nrhs, 256)), dim3(256), 0, s,
                        lam, L0.b.get(), n * nrhs);
     LAIR_LAUNCH_CHECK();
