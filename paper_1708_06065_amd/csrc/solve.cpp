@@ -974,7 +974,7 @@ lair_status solve_fgmres_impl(lair_hierarchy *h, const double *b, double *x,
         bb = h->bscaled.get();
     }
     CsrView<double> A0 = view<double>(L0.A, L0.team_A);
-    DevArr<double> V, Z, w, coef, dots, partial, scale;
+    DevArr<double> V, Z, w, coef, dots, partial;
     V.alloc((size_t)(m + 1) * nv, s);
     Z.alloc((size_t)m * nv, s);
     w.alloc((size_t)nv, s);
@@ -983,7 +983,6 @@ lair_status solve_fgmres_impl(lair_hierarchy *h, const double *b, double *x,
     const size_t HOFF = (size_t)(m + 1) * R;
     dots.alloc(2 * HOFF + R, s);
     partial.alloc((size_t)kry_dot_blocks(nv) * (m + 1) * R, s);
-    scale.alloc((size_t)R, s);
     double *Vp = V.get(), *Zp = Z.get();
     auto Vk = [&](int k) { return Vp + (int64_t)k * nv; };
     auto Zk = [&](int k) { return Zp + (int64_t)k * nv; };
@@ -1043,18 +1042,15 @@ lair_status solve_fgmres_impl(lair_hierarchy *h, const double *b, double *x,
             g[q] = act[q] ? beta[q] : 0.0;
             for (size_t i = 1; i < H1; ++i) g[i * R + q] = 0.0;
         }
-        upload(scale.get(), sc);
-        op_scale_rhs(n, R, Vk(0), scale.get(), Vk(0), s);
+        op_scale_rhs(n, R, Vk(0), sc.data(), Vk(0), s);
         for (int j = 0; j < m; ++j) {
             precond(Vk(j), Zk(j));
             op_spmv<double>(A0, Zk(j), w.get(), R, false, s);
             // Gram-Schmidt twice: c = V^T w, w -= V c; h = c1 + c2
-            for (int pass = 0; pass < 2; ++pass) {
-                double *cd = dots.get() + (size_t)pass * HOFF;
-                op_mdot(n, R, Vp, nv, j + 1, w.get(), partial.get(), cd, s);
-                op_maxpy(n, R, Vp, nv, j + 1, cd, w.get(), s);
-            }
-            op_mdot(n, R, w.get(), nv, 1, w.get(), partial.get(), dots.get() + 2 * HOFF, s);
+            double *c1 = dots.get(), *c2 = c1 + HOFF;
+            op_mdot(n, R, Vp, nv, j + 1, w.get(), partial.get(), c1, s);
+            op_gram_schmidt(n, R, Vp, nv, j + 1, c1, w.get(), true, partial.get(), c2, s);
+            op_gram_schmidt(n, R, Vp, nv, j + 1, c2, w.get(), false, partial.get(), c2 + HOFF, s);
             {
                 Readback rb(s);
                 rb.add(hc.data(), dots.get(), sizeof(double) * (j + 1) * R);
@@ -1100,8 +1096,7 @@ lair_status solve_fgmres_impl(lair_hierarchy *h, const double *b, double *x,
                 }
             }
             if (!still || it >= maxit || j + 1 == m) break;
-            upload(scale.get(), sc);
-            op_scale_rhs(n, R, w.get(), scale.get(), Vk(j + 1), s);
+            op_scale_rhs(n, R, w.get(), sc.data(), Vk(j + 1), s);
         }
         // x += Z y, y from the triangular systems (each right-hand side its
         // own number of steps; missing steps weigh zero)
