@@ -29,7 +29,9 @@ __device__ __forceinline__ VT src_val(const VT *xF, const VT *xC, const int8_t *
 // entry of the row).  A lane loads four of its entries, then their four
 // gathers, before it sums them in entry order, so the loads of a row are in
 // flight together (the sums are those of the plain loop).
-template <class VT, int T, bool SEL>
+// TAG: the columns carry the point type in their sign bit, which spares SEL a
+// gather of cf beside each gather of the source.
+template <class VT, int T, bool SEL, bool TAG = false>
 __device__ __forceinline__ void row_acc1(int lo, int hi, int lane, int diag_col,
                                          const int32_t *cj, const VT *v,
                                          const VT *xF, const VT *xC,
@@ -44,9 +46,19 @@ __device__ __forceinline__ void row_acc1(int lo, int hi, int lane, int diag_col,
             c[u] = p < hi ? cj[p] : -1;
             a[u] = p < hi ? v[p] : (VT)0;
         }
+        if (TAG) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            xv[u] = c[u] >= 0 ? src_val<VT, SEL>(xF, xC, cf, c[u], c[u]) : (VT)0;
+            for (int u = 0; u < U; ++u) {
+                const bool in = p0 + u * T < hi;
+                const int col = c[u] & 0x7fffffff;
+                xv[u] = in ? (c[u] < 0 ? xC : xF)[col] : (VT)0;
+                c[u] = in ? col : -1;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                xv[u] = c[u] >= 0 ? src_val<VT, SEL>(xF, xC, cf, c[u], c[u]) : (VT)0;
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (c[u] >= 0) {
@@ -415,10 +427,12 @@ k_rowdot1(int32_t nrows, const int32_t *rp, const int32_t *cj, const VT *v,
 // One right-hand side over a listed subset of rows: rows[k] for k < *cnt
 // (the list and its length live on the device; the grid covers the list's
 // capacity).
-template <class VT, int T, int MODE>
+// With y2 the result is also written there (as YT: a work vector, or the
+// float copy of a residual).
+template <class VT, int T, int MODE, class YT>
 __global__ void __launch_bounds__(256)
 k_rowdot_list(const int32_t *rows, const int32_t *cnt, const int32_t *rp, const int32_t *cj,
-              const VT *v, const VT *x, const VT *b, VT *y) {
+              const VT *v, const VT *x, const VT *b, VT *y, YT *y2) {
     const int64_t gt = xcd_block_id() * blockDim.x + threadIdx.x;
     const int lane = (int)(gt % T);
     const int64_t nteams = (int64_t)gridDim.x * (blockDim.x / T);
@@ -429,9 +443,11 @@ k_rowdot_list(const int32_t *rows, const int32_t *cnt, const int32_t *rp, const 
         row_acc1<VT, T, false>(rp[i], rp[i + 1], lane, -1, cj, v, x, x, nullptr, acc, d);
         acc = team_sum<T>(acc);
         if (lane == 0) {
-            if (MODE == MODE_RESID) y[i] = b[i] - acc;
-            else if (MODE == MODE_SET) y[i] = acc;
-            else y[i] += acc;
+            VT r = acc;
+            if (MODE == MODE_RESID) r = b[i] - acc;
+            else if (MODE == MODE_ADD) r = y[i] + acc;
+            y[i] = r;
+            if (y2) y2[i] = (YT)r;
         }
     }
 }
@@ -563,12 +579,12 @@ bool op_spmv_split_ok(int32_t nrhs, const void *x, const void *x_hi, const void 
     return nrhs == 1 || (aligned16(x) && aligned16(x_hi) && aligned16(y));
 }
 
-template <class VT, int MODE>
+template <class VT, int MODE, class YT>
 static void rowdot_list_t(const CsrView<VT> &A, const int32_t *rows, const int32_t *cnt,
-                          int32_t cap, const VT *x, const VT *b, VT *y, hipStream_t s) {
+                          int32_t cap, const VT *x, const VT *b, VT *y, YT *y2, hipStream_t s) {
 #define LAIR_RL(TT)                                                                    \
-    LAIR_LAUNCH((k_rowdot_list<VT, TT, MODE>), dim3(list_grid((int64_t)cap * TT)),     \
-                dim3(256), 0, s, rows, cnt, A.rp, A.cj, A.v, x, b, y)
+    LAIR_LAUNCH((k_rowdot_list<VT, TT, MODE, YT>), dim3(list_grid((int64_t)cap * TT)), \
+                dim3(256), 0, s, rows, cnt, A.rp, A.cj, A.v, x, b, y, y2)
     switch (scalar_team(A.team)) {
         case 1: LAIR_RL(1); break;
         case 2: LAIR_RL(2); break;
@@ -584,11 +600,18 @@ static void rowdot_list_t(const CsrView<VT> &A, const int32_t *rows, const int32
 
 template <class VT>
 void op_rowdot_list(const CsrView<VT> &A, int mode, const int32_t *rows, const int32_t *cnt,
-                    int32_t cap, const VT *x, const VT *b, VT *y, hipStream_t s) {
+                    int32_t cap, const VT *x, const VT *b, VT *y, hipStream_t s, VT *y2) {
     if (cap == 0) return;
-    if (mode == MODE_RESID) rowdot_list_t<VT, MODE_RESID>(A, rows, cnt, cap, x, b, y, s);
-    else if (mode == MODE_SET) rowdot_list_t<VT, MODE_SET>(A, rows, cnt, cap, x, b, y, s);
-    else rowdot_list_t<VT, MODE_ADD>(A, rows, cnt, cap, x, b, y, s);
+    if (mode == MODE_RESID) rowdot_list_t<VT, MODE_RESID>(A, rows, cnt, cap, x, b, y, y2, s);
+    else if (mode == MODE_SET) rowdot_list_t<VT, MODE_SET>(A, rows, cnt, cap, x, b, y, y2, s);
+    else rowdot_list_t<VT, MODE_ADD>(A, rows, cnt, cap, x, b, y, y2, s);
+}
+
+void op_residual_list(const CsrView<double> &A, const int32_t *rows, const int32_t *cnt,
+                      int32_t cap, const double *x, const double *b, double *r, float *r32,
+                      hipStream_t s) {
+    if (cap == 0) return;
+    rowdot_list_t<double, MODE_RESID>(A, rows, cnt, cap, x, b, r, r32, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -596,7 +619,7 @@ void op_rowdot_list(const CsrView<VT> &A, int mode, const int32_t *rows, const i
 // i = X[k], written to out[k] (compact) or out[i].  Every row reads the
 // previous iterate; the diagonal is found while streaming the row.
 // ---------------------------------------------------------------------------
-template <class VT, int T, bool SEL>
+template <class VT, int T, bool SEL, bool TAG>
 __global__ void __launch_bounds__(256)
 k_jacobi1(int32_t nx, const int32_t *cnt, const int32_t *rows, int32_t row0, const int32_t *rp,
           const int32_t *cj, const VT *v, const VT *b, const VT *xF, const VT *xC,
@@ -608,7 +631,7 @@ k_jacobi1(int32_t nx, const int32_t *cnt, const int32_t *rows, int32_t row0, con
     for (int64_t k = gt / T; k < n; k += nteams) {
         const int32_t i = list_row(rows, row0, k);
         VT acc = (VT)0, d = (VT)0;
-        row_acc1<VT, T, SEL>(rp[i], rp[i + 1], lane, i, cj, v, xF, xC, cf, acc, d);
+        row_acc1<VT, T, SEL, TAG>(rp[i], rp[i + 1], lane, i, cj, v, xF, xC, cf, acc, d);
         acc = team_sum<T>(acc);
         d = team_sum<T>(d);
         if (lane == 0) {
@@ -689,9 +712,14 @@ static void jacobi_launch(const CsrView<VT> &A, const int32_t *rows, int32_t row
         return;
     }
 #define LAIR_JC(TT)                                                              \
-    LAIR_LAUNCH((k_jacobi1<VT, TT, SEL>),                                 \
-                       dim3(cnt ? list_grid((int64_t)nx * TT) : blocks_for((int64_t)nx * TT, 256)), \
-                       dim3(256), 0, s, nx, cnt, rows, row0, A.rp, A.cj, A.v, b, xF, xC, cf, out, compact, om)
+    if (SEL && A.cjt)                                                            \
+        LAIR_LAUNCH((k_jacobi1<VT, TT, SEL, true>),                              \
+                    dim3(cnt ? list_grid((int64_t)nx * TT) : blocks_for((int64_t)nx * TT, 256)), \
+                    dim3(256), 0, s, nx, cnt, rows, row0, A.rp, A.cjt, A.v, b, xF, xC, cf, out, compact, om); \
+    else                                                                         \
+        LAIR_LAUNCH((k_jacobi1<VT, TT, SEL, false>),                             \
+                    dim3(cnt ? list_grid((int64_t)nx * TT) : blocks_for((int64_t)nx * TT, 256)), \
+                    dim3(256), 0, s, nx, cnt, rows, row0, A.rp, A.cj, A.v, b, xF, xC, cf, out, compact, om)
     switch (scalar_team(A.team)) {
         case 1: LAIR_JC(1); break;
         case 2: LAIR_JC(2); break;
@@ -1221,8 +1249,8 @@ template void op_spmv<double>(const CsrView<double> &, const double *, double *,
 template void op_spmv<float>(const CsrView<float> &, const float *, float *, int32_t, bool, hipStream_t, const float *, int32_t, const int8_t *);
 template void op_jacobi<double>(const CsrView<double> &, const int32_t *, int32_t, const double *, const double *, const double *, const int8_t *, double *, bool, double, int32_t, hipStream_t, const int32_t *, int32_t);
 template void op_jacobi<float>(const CsrView<float> &, const int32_t *, int32_t, const float *, const float *, const float *, const int8_t *, float *, bool, double, int32_t, hipStream_t, const int32_t *, int32_t);
-template void op_rowdot_list<double>(const CsrView<double> &, int, const int32_t *, const int32_t *, int32_t, const double *, const double *, double *, hipStream_t);
-template void op_rowdot_list<float>(const CsrView<float> &, int, const int32_t *, const int32_t *, int32_t, const float *, const float *, float *, hipStream_t);
+template void op_rowdot_list<double>(const CsrView<double> &, int, const int32_t *, const int32_t *, int32_t, const double *, const double *, double *, hipStream_t, double *);
+template void op_rowdot_list<float>(const CsrView<float> &, int, const int32_t *, const int32_t *, int32_t, const float *, const float *, float *, hipStream_t, float *);
 template void op_update_list<double>(const int32_t *, const int32_t *, int32_t, double *, const double *, hipStream_t);
 template void op_update_list<float>(const int32_t *, const int32_t *, int32_t, double *, const float *, hipStream_t);
 template void op_coarse_apply<double>(int32_t, const double *, const double *, double *, int32_t, bool, hipStream_t);

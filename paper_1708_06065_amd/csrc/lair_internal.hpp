@@ -471,9 +471,15 @@ void op_dense_solve(int32_t n, const double *lu, const int32_t *piv,
 // per right-hand side sum of squares into out[0..nrhs) (double, fixed order)
 // One right-hand side over the listed rows rows[k], k < *cnt (device list of
 // capacity cap): mode 0 y = b - A x, 1 y = A x, 2 y += A x.
+// y2 (optional) gets the result too; op_residual_list writes r = b - A x and
+// its float copy (optional).
 template <class VT>
 void op_rowdot_list(const CsrView<VT> &A, int mode, const int32_t *rows, const int32_t *cnt,
-                    int32_t cap, const VT *x, const VT *b, VT *y, hipStream_t s);
+                    int32_t cap, const VT *x, const VT *b, VT *y, hipStream_t s,
+                    VT *y2 = nullptr);
+void op_residual_list(const CsrView<double> &A, const int32_t *rows, const int32_t *cnt,
+                      int32_t cap, const double *x, const double *b, double *r, float *r32,
+                      hipStream_t s);
 // x[i] += e[i] for the listed rows
 template <class ET>
 void op_update_list(const int32_t *rows, const int32_t *cnt, int32_t cap, double *x,

@@ -129,10 +129,35 @@ static bool ffc(lair_hierarchy *h, Level &Lv, const VT *b, VT *x, int32_t nrhs,
     // split ordering: F rows are 0 .. nf-1 and C rows nf .. n-1 (no list)
     const int32_t *frows = act ? Lv.act_f.get() : (split ? nullptr : Lv.flist.get());
     const int32_t *fcnt = act ? Lv.act_cnt + 1 : nullptr;
+    if (act) {
+        // the interpolation has written X and Y alike: F sweep 1 reads X and
+        // writes Y's F rows, F sweep 2 reads Y and writes X's, and the C sweep
+        // reads X at F-points and Y at C-points and writes X's C rows in place
+        const int32_t ncr = Lv.nrc >= 0 ? Lv.nrc : Lv.nc;
+        CsrView<VT> At = A;
+        At.cjt = Lv.cjt.get();
+        {
+            ProfScope ps("jacobi", s, ab_jacobi(Lv.nnzF, Lv.nf, Lv.n, w, 1, false),
+                         2.0 * Lv.nnzF);
+            op_jacobi<VT>(A, frows, Lv.nf, b, x, x, nullptr, y, false, om, 1, s, fcnt);
+        }
+        {
+            ProfScope ps("jacobi", s, ab_jacobi(Lv.nnzF, Lv.nf, Lv.n, w, 1, false),
+                         2.0 * Lv.nnzF);
+            op_jacobi<VT>(A, frows, Lv.nf, b, y, y, nullptr, x, false, om, 1, s, fcnt);
+        }
+        {
+            ProfScope ps("jacobi", s, ab_jacobi(Lv.nnzC, ncr, Lv.n, w, 1, true),
+                         2.0 * Lv.nnzC);
+            op_jacobi<VT>(At, Lv.act_c.get(), ncr, b, x, y, Lv.cf.get(), x, false, om, 1, s,
+                          Lv.act_cnt + 2);
+        }
+        return false;
+    }
     {
         ProfScope ps("jacobi", s, ab_jacobi(Lv.nnzF, Lv.nf, Lv.n, w, nrhs, false),
                      2.0 * Lv.nnzF * nrhs);
-        op_jacobi<VT>(A, frows, Lv.nf, b, x, x, nullptr, y, false, om, nrhs, s, fcnt);
+        op_jacobi<VT>(A, frows, Lv.nf, b, x, x, nullptr, y, false, om, nrhs, s);
     }
     {
         ProfScope ps("jacobi", s, ab_jacobi(Lv.nnzF, Lv.nf, Lv.n, w, nrhs, true),
@@ -140,24 +165,22 @@ static bool ffc(lair_hierarchy *h, Level &Lv, const VT *b, VT *x, int32_t nrhs,
         CsrView<VT> At = A;
         At.cjt = split ? Lv.cjt_split.get() : Lv.cjt.get();
         op_jacobi<VT>(At, frows, Lv.nf, b, y, x, split ? Lv.cf_split.get() : Lv.cf.get(), x,
-                      false, om, nrhs, s, fcnt);
+                      false, om, nrhs, s);
     }
-    const int32_t *crows = act ? Lv.act_c.get()
-                               : split ? nullptr
-                               : (Lv.nrc >= 0 ? Lv.rclist.get() : Lv.clist.get());
-    const int32_t *ccnt = act ? Lv.act_cnt + 2 : nullptr;
+    const int32_t *crows = split ? nullptr
+                                 : (Lv.nrc >= 0 ? Lv.rclist.get() : Lv.clist.get());
     const int32_t ncr = Lv.nrc >= 0 ? Lv.nrc : Lv.nc;
     const int32_t c0 = split ? Lv.nf : 0;
-    leave_c = leave_c && !act && Lv.nrc < 0;
+    leave_c = leave_c && Lv.nrc < 0;
     {
         ProfScope ps("jacobi", s, ab_jacobi(Lv.nnzC, ncr, Lv.n, w, nrhs, false),
                      2.0 * Lv.nnzC * nrhs);
-        op_jacobi<VT>(A, crows, ncr, b, x, x, nullptr, y, !leave_c, om, nrhs, s, ccnt, c0);
+        op_jacobi<VT>(A, crows, ncr, b, x, x, nullptr, y, !leave_c, om, nrhs, s, nullptr, c0);
     }
     if (leave_c) return true;
     {
         ProfScope ps("scatter", s, 4.0 * ncr + 2.0 * w * nrhs * ncr);
-        op_scatter<VT>(crows, ncr, y, x, nrhs, s, ccnt, c0);
+        op_scatter<VT>(crows, ncr, y, x, nrhs, s, nullptr, c0);
     }
     return false;
 }
@@ -598,7 +621,8 @@ static const VT *vcycle(lair_hierarchy *h, size_t l, const VT *b, VT *x, bool x_
                      2.0 * Lv.P.nnz * nrhs);
         if (h->use_act)
             op_rowdot_list<VT>(view<VT>(Lv.P, Lv.team_P), x_zero ? 1 : 2, Lv.act_p.get(),
-                               Lv.act_cnt + 3, Lv.n, xc, nullptr, x, s);
+                               Lv.act_cnt + 3, Lv.n, xc, nullptr, x, s,
+                               vec<VT>(Lv.t, Lv.t32));
         else
             op_spmv<VT>(view<VT>(Lv.Ps.rp.get() ? Lv.Ps : Lv.P, Lv.team_P), xc, x, nrhs, !x_zero,
                         s, xc_hi, Nx.split && nrhs > 1 ? Nx.nf : -1,
@@ -1141,6 +1165,10 @@ lair_status solve_fgmres_impl(lair_hierarchy *h, const double *b, double *x,
     return relmax <= rtol ? LAIR_OK : LAIR_ENOCONV;
 }
 
+// Longest run of a row list that one workgroup copies (whole runs, up to
+// 102,400 rows, took 54 us a rebuild on 24 systems and 92 us on 512).
+static const int32_t ACT_PIECE = 4096;
+
 // The union's vectors that the systems' tails read and write.
 static void set_batch_vectors(lair_hierarchy *h, bool mixed) {
     for (size_t l = 0; l < h->L.size(); ++l) {
@@ -1182,7 +1210,8 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     const bool lists = ns > 1;
     const size_t cnt_bytes = (4 * sizeof(int32_t) * h->L.size() + 15) & ~(size_t)15;
     if (lists && L0.act_cnt == nullptr) {
-        const size_t maxseg = 4 * h->L.size() * (size_t)ns;
+        size_t maxseg = 4 * h->L.size() * (size_t)ns;
+        for (auto &lp : h->L) maxseg += 4 * (size_t)lp->n / ACT_PIECE;
         h->act_upload.alloc(cnt_bytes + sizeof(int64_t) * (maxseg + 1) +
                                 3 * sizeof(int32_t) * maxseg + 64, s);
         for (size_t l = 0; l < h->L.size(); ++l) {
@@ -1306,11 +1335,15 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
                     const int32_t len = runs[l][k][q + 1] - runs[l][k][q];
                     if (len == 0) continue;
                     const int32_t start = k == 0 ? (int32_t)h->L[l]->seg[q] : runs[l][k][q];
-                    out.push_back(out.back() + len);
-                    src.push_back(start);
-                    dst.push_back(pos);
-                    lst.push_back((int32_t)(4 * l + t));
-                    pos += len;
+                    // a workgroup copies a run, long ones in pieces
+                    for (int32_t o = 0; o < len; o += ACT_PIECE) {
+                        const int32_t m = std::min(ACT_PIECE, len - o);
+                        out.push_back(out.back() + m);
+                        src.push_back(start + o);
+                        dst.push_back(pos);
+                        lst.push_back((int32_t)(4 * l + t));
+                        pos += m;
+                    }
                 }
                 counts[4 * l + t] = pos;
             }
@@ -1357,6 +1390,8 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
         seg_norms(h->r0.get(), nullptr, st);
     };
     residual_and_norms(s);
+    // later residuals are written with their float copy
+    if (mixed && lists) op_cast_f32(h->r0.get(), h->r0_32.get(), n, s);
     read_norms(h->seg_norm.get(), ns, s, rn);
     rfirst = rn;
     h->active.assign((size_t)ns, 1);
@@ -1393,7 +1428,7 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
         run_iteration(h, mixed ? IT_BATCH_MIXED : IT_BATCH_FP64, 1, bb, x, s,
                       [&](hipStream_t st) {
             if (mixed) {
-                {
+                if (!lists) {
                     ProfScope ps("cast", st, 12.0 * n);
                     op_cast_f32(h->r0.get(), h->r0_32.get(), n, st);
                 }
@@ -1418,8 +1453,8 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
             {
                 ProfScope ps("residual", st, ab_rowdot(L0.A, 8, 1, 2), 2.0 * L0.A.nnz);
                 if (lists)
-                    op_rowdot_list<double>(A0, 0, L0.act_rows.get(), L0.act_cnt,
-                                           (int32_t)n, x, bb, h->r0.get(), st);
+                    op_residual_list(A0, L0.act_rows.get(), L0.act_cnt, (int32_t)n, x, bb,
+                                     h->r0.get(), mixed ? h->r0_32.get() : nullptr, st);
                 else
                     op_residual<double>(A0, bb, x, h->r0.get(), 1, st);
             }
