@@ -268,88 +268,7 @@ void launch_seg_sumsq_blocks(int32_t nsys, int32_t nblk, const int32_t *bsys,
     LAIR_LAUNCH_CHECK();
 }
 
-// Systems whose coarsest block has at most 64 rows: one wave per system does
-// the LU with partial pivoting and the inverse in LDS (the block and the
-// inverse, 32 KB each).  Ties in the pivot search go to the smallest row,
-// as in k_block_lu, so the factors and pivots are the same.
-constexpr int SMALL_DENSE = 64;
-
-__global__ void __launch_bounds__(64)
-k_block_lu_inv_small(const int64_t *seg, const int64_t *doff, double *dense, int32_t *piv,
-                     double *inv, int32_t *info) {
-    __shared__ double a[SMALL_DENSE * SMALL_DENSE];
-    __shared__ double x[SMALL_DENSE * SMALL_DENSE];
-    __shared__ int32_t spv[SMALL_DENSE];
-    const int32_t s = blockIdx.x;
-    const int n = (int)(seg[s + 1] - seg[s]);
-    if (n > SMALL_DENSE) return;
-    const int t = threadIdx.x;
-    double *g = dense + doff[s];
-    for (int e = t; e < n * n; e += 64) a[e] = g[e];
-    wave_lds_sync();
-    int32_t *pv = piv + seg[s];
-    for (int k = 0; k < n; ++k) {
-        double bv = -1.0;
-        int bi = INT_MAX;
-        if (t >= k && t < n) { bv = fabs(a[t * n + k]); bi = t; }
-        team_argmax<WAVE>(bv, bi);
-        if (bv == 0.0) {
-            if (t == 0) atomicMax(info, s + 1);
-            return;
-        }
-        if (t == 0) { pv[k] = bi; spv[k] = bi; }
-        if (bi != k && t < n) {
-            double q = a[k * n + t];
-            a[k * n + t] = a[bi * n + t];
-            a[bi * n + t] = q;
-        }
-        wave_lds_sync();
-        const double inv_p = 1.0 / a[k * n + k];
-        if (t > k && t < n) {
-            const double l = a[t * n + k] * inv_p;
-            a[t * n + k] = l;
-            for (int j = k + 1; j < n; ++j) a[t * n + j] -= l * a[k * n + j];
-        }
-        wave_lds_sync();
-    }
-    for (int e = t; e < n * n; e += 64) g[e] = a[e];
-    // inverse: lane j solves K x = e_j
-    if (t < n) {
-        for (int i = 0; i < n; ++i) x[i * n + t] = (i == t) ? 1.0 : 0.0;
-        for (int k = 0; k < n; ++k) {
-            const int p = spv[k];
-            if (p != k) {
-                double q = x[k * n + t];
-                x[k * n + t] = x[p * n + t];
-                x[p * n + t] = q;
-            }
-        }
-        for (int k = 0; k < n; ++k) {
-            const double xk = x[k * n + t];
-            for (int i = k + 1; i < n; ++i) x[i * n + t] -= a[i * n + k] * xk;
-        }
-        for (int k = n - 1; k >= 0; --k) {
-            const double xk = x[k * n + t] / a[k * n + k];
-            x[k * n + t] = xk;
-            for (int i = 0; i < k; ++i) x[i * n + t] -= a[i * n + k] * xk;
-        }
-    }
-    wave_lds_sync();
-    double *o = inv + doff[s];
-    for (int e = t; e < n * n; e += 64) o[e] = x[e];
-}
-
-void launch_block_lu_inv_small(int32_t nsys, const int64_t *seg, const int64_t *doff,
-                               double *dense, int32_t *piv, double *inv, int32_t *info,
-                               hipStream_t s) {
-    LAIR_LAUNCH(k_block_lu_inv_small, dim3(nsys), dim3(64), 0, s, seg, doff, dense, piv, inv,
-                info);
-    LAIR_LAUNCH_CHECK();
-}
-
-int32_t small_dense_max() { return SMALL_DENSE; }
-
-// Inverse of a block of 65..256 rows from its LU factors (P K = L U): one
+// Inverse of a block of 129..256 rows from its LU factors (P K = L U): one
 // wave per chunk of 32 columns of the inverse (blockIdx.y), the chunk held in
 // LDS (at most 256 x 32 doubles).  Lanes take a column each and one of two
 // row parities; rows of L and U are read from global memory.
@@ -357,12 +276,13 @@ constexpr int MID_DENSE = 256, MID_COLS = 32;
 
 __global__ void __launch_bounds__(64)
 k_block_inv_mid(const int64_t *seg, const int64_t *doff, const double *__restrict__ lu,
-                const int32_t *piv, double *__restrict__ inv, const uint8_t *use_inv) {
+                const int32_t *piv, double *__restrict__ inv, const uint8_t *use_inv,
+                int gj_rows) {
     __shared__ double y[MID_DENSE * MID_COLS];
     const int32_t s = blockIdx.x;
     if (!use_inv[s]) return;
     const int n = (int)(seg[s + 1] - seg[s]);
-    if (n <= SMALL_DENSE || n > MID_DENSE) return;
+    if (n <= gj_rows || n > MID_DENSE) return;
     const int j0 = blockIdx.y * MID_COLS;
     if (j0 >= n) return;
     const int c = threadIdx.x % MID_COLS, par = threadIdx.x / MID_COLS;
@@ -401,7 +321,7 @@ void launch_block_inv_mid(int32_t nsys, int32_t maxn, const int64_t *seg, const 
                           const uint8_t *use_inv, hipStream_t s) {
     const int gy = (maxn + MID_COLS - 1) / MID_COLS;
     LAIR_LAUNCH(k_block_inv_mid, dim3(nsys, gy), dim3(64), 0, s, seg, doff, lu, piv, inv,
-                use_inv);
+                use_inv, gj_max());
     LAIR_LAUNCH_CHECK();
 }
 

@@ -397,8 +397,8 @@ size_t max_lds_per_block();
 // dense coarsest factorisation
 void launch_dense_from_csr(int32_t n, const int32_t *rp, const int32_t *cj,
                            const double *v, double *dense, hipStream_t s);
-// n <= 128 and n^2 doubles fit one workgroup's LDS: the explicit inverse of
-// the dense matrix by Gauss-Jordan in one kernel; false when it does not apply
+// n <= 128: the explicit inverse of the dense matrix by Gauss-Jordan in one
+// kernel; false when it does not apply
 bool launch_dense_gj_inv(int32_t n, const double *dense, double *inv, int32_t *info,
                          hipStream_t s);
 void launch_dense_lu(int32_t n, double *lu, int32_t *piv, int32_t *info,
@@ -577,16 +577,16 @@ void launch_dense_blocks(int32_t nsys, const int64_t *seg, const int64_t *doff,
                          double *dense, int64_t nrows, hipStream_t s);
 void launch_block_lu(int32_t nsys, const int64_t *seg, const int64_t *doff, double *dense,
                      int32_t *piv, int32_t *info, hipStream_t s, int32_t min_n = 0);
-// blocks of at most small_dense_max() rows: LU and inverse in one kernel
-int32_t small_dense_max();
-// blocks of small_dense_max()+1 .. mid_dense_max() rows: inverse from the LU
+// blocks of at most gj_max() rows: their inverses in one kernel, a workgroup
+// each (info: zeroed by the caller)
+int32_t gj_max();
+void launch_gj_inv_batch(int32_t nsys, const int64_t *seg, const int64_t *doff,
+                         const double *dense, double *inv, int32_t *info, hipStream_t s);
+// blocks of gj_max() + 1 .. mid_dense_max() rows: inverse from the LU
 int32_t mid_dense_max();
 void launch_block_inv_mid(int32_t nsys, int32_t maxn, const int64_t *seg, const int64_t *doff,
                           const double *lu, const int32_t *piv, double *inv,
                           const uint8_t *use_inv, hipStream_t s);
-void launch_block_lu_inv_small(int32_t nsys, const int64_t *seg, const int64_t *doff,
-                               double *dense, int32_t *piv, double *inv, int32_t *info,
-                               hipStream_t s);
 void launch_block_solve(int32_t nsys, const int64_t *seg, const int64_t *doff,
                         const double *dense, const int32_t *piv, const double *b, double *x,
                         bool transpose, hipStream_t s, const uint8_t *active = nullptr,
