@@ -1807,57 +1807,279 @@ k_local_node(int32_t nnode, int32_t k, const int32_t *clist, const int32_t *nptr
     }
 }
 
+// Largest of a wave's values, in every lane's scalar registers.
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+#define LAIR_DPP_MAX(CTRL)                                                                  \
+    {                                                                                       \
+        const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);                          \
+        const uint32_t l2 = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);     \
+        const uint32_t h2 = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);     \
+        const uint64_t o = ((uint64_t)h2 << 32) | l2;                                       \
+        v = o > v ? o : v;                                                                  \
+    }
+    LAIR_DPP_MAX(0x111)      // row_shr:1
+    LAIR_DPP_MAX(0x112)      // row_shr:2
+    LAIR_DPP_MAX(0x114)      // row_shr:4
+    LAIR_DPP_MAX(0x118)      // row_shr:8
+    LAIR_DPP_MAX(0x142)      // row_bcast:15
+    LAIR_DPP_MAX(0x143)      // row_bcast:31
+#undef LAIR_DPP_MAX
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, 63);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), 63);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // The node solve with M in registers, for systems up to 8R rows.  The wave
 // is an 8 x 8 grid of lanes: lane (lr, lq) keeps the entries (r, q) of M
 // with r = lr + 8i, q = lq + 8j in m[i][j], and in column slot R the entry
-// of right-hand side lq (lq < k) at row r.  Rows never move: each keeps its
-// position under the row exchanges beside it, and the pivot of step kk is
-// the arg-max of |M[r][kk]| over the rows at positions >= kk, ties to the
-// smallest position, as in the LDS form.  Every lane of a row of lanes
-// holds column kk of its rows (cur), so the arg-max needs only a reduction
-// across the rows of lanes and every lane forms its rows' multipliers; the
-// pivot row goes through LDS from its row of lanes, and after the update the
-// next column is shared along each row of lanes.  The substitutions
-// take the column of U or L the same way; in MIXED the refinement's
-// residual f - M z comes from the double matrix in LDS, summed in the order
-// of the LDS form.  Every
+// of right-hand side lq (lq < k) at row r.  Rows do not move in the
+// elimination: each keeps its position under the row exchanges beside it, and
+// the pivot of step kk is the arg-max of |M[r][kk]| over the rows at positions
+// >= kk, ties to the smallest position, as in the LDS form.  Column kk goes
+// through LDS, one row (two above 64 rows) per lane, for the pivot and the
+// multipliers; those and the pivot row come back as a few wide reads.  Then
+// the rows are put in order, so that the substitutions know at compile time
+// which slot a step concerns.  In MIXED the refinement's residual f - M z
+// comes from the double matrix, summed in the order of the LDS form.  Every
 // entry sees the operations of the LDS form in the same order, so the rows
-// of R are the same bit for bit.  LDS holds the gathered matrix in double,
-// the right-hand sides and the neighbourhood.
+// of R are the same bit for bit.
+//
+// What bounds it is the number of instructions of a step, times 4s steps, in
+// two waves per SIMD (the registers of the largest classes).  The matrix is
+// gathered as the rows of A, so that a wave reads a column of M side by side;
+// a hash of N finds a column's place in one or two reads where a search took
+// seven; blocks of eight steps are instances of templates, since as a loop
+// unrolled by pragma the compiler kept m of the largest class in scratch.
+// 21843 systems of 72 rows with 6 right-hand sides, mixed: 4.55 -> 2.23 ms;
+// 65536 of 12 and 18 rows 0.98 -> 0.58 ms; a launch with a few of up to 72 rows
+// 0.41 -> 0.18 ms, of up to 104 rows (in LDS before) 0.7 to 1.5 -> 0.26 to 0.56 ms.
 template <int R>
-__host__ __device__ constexpr size_t node_reg_lds_bytes(int k, bool mg_in_lds = true) {
-    return (mg_in_lds ? (size_t)64 * R * R * sizeof(double) : 0) +
-           2 * (size_t)k * 8 * R * sizeof(double) +
-           2 * (size_t)8 * (R + 1) * sizeof(double) + (4 * (size_t)8 * R + 1) * sizeof(int32_t) +
-           64;
+struct NodeReg {
+    static constexpr int SC = 8 * R, C = R + 1;
+    static constexpr int CP = (C + 3) / 4 * 4, RP = (R + 3) / 4 * 4;    // padded for wide reads
+    static constexpr int HB = R <= 3 ? 6 : R <= 5 ? 7 : 8, HN = 1 << HB;
+    static_assert(SC * 2 <= HN, "the hash of N is at most half full");
+    static constexpr size_t lds_bytes(int k, bool mg_in_lds, size_t ft) {
+        return (mg_in_lds ? (size_t)SC * SC * sizeof(double) : 0) +
+               ((size_t)k + 8) * SC * sizeof(double) + (8 * CP + 16 * RP) * ft +
+               (4 * SC + HN) * sizeof(int32_t) + HN;
+    }
+};
+
+// A wave's LDS for one system.
+template <int R, class FT>
+struct NodeShared {
+    double *f, *z;              // f[k][s]; z[s][8], also the exchange of rows
+    FT *prow, *col, *mul;       // [lq][j], [lr][i], [lr][i]
+    int32_t *ln, *st, *en, *rowat, *hkey;
+    uint8_t *hpos;
+    __device__ NodeShared(double *base, int k) {
+        using N = NodeReg<R>;
+        f = base;
+        z = f + (size_t)k * N::SC;
+        prow = (FT *)(z + (size_t)8 * N::SC);
+        col = prow + 8 * N::CP;
+        mul = col + 8 * N::RP;
+        ln = (int32_t *)(mul + 8 * N::RP);
+        st = ln + N::SC;
+        en = st + N::SC;
+        rowat = en + N::SC;
+        hkey = rowat + N::SC;
+        hpos = (uint8_t *)(hkey + N::HN);
+    }
+    __device__ uint32_t slot(int32_t c) const {
+        return ((uint32_t)c * 2654435761u) >> (32 - NodeReg<R>::HB);
+    }
+    // the place of column c in N, or -1
+    __device__ int place(int32_t c) const {
+        uint32_t h = slot(c);
+        for (;;) {
+            const int32_t x = hkey[h];
+            if (x == c) return hpos[h];
+            if (x < 0) return -1;
+            h = (h + 1) & (NodeReg<R>::HN - 1);
+        }
+    }
+};
+
+// Steps 8 JB .. of the elimination and all after them; true: singular.
+// pos[i]: the position of row lr + 8i; at0, at1: of rows lane and 64 + lane.
+// Column kk of M is in sh.col when step kk begins.
+template <int JB, int R, class FT>
+__device__ __forceinline__ bool node_eliminate(FT (&m)[R][R + 1], int (&pos)[R], int &at0, int &at1,
+                                               int s, int lane, double tol,
+                                               const NodeShared<R, FT> &sh) {
+    if constexpr (JB < R) {
+        using N = NodeReg<R>;
+        const int lr = lane >> 3, lq = lane & 7;
+        const int k1 = min(s, 8 * JB + 8);
+        const int a0 = (lane & 7) * N::RP + (lane >> 3), a1 = a0 + 8;   // rows lane, 64 + lane
+#pragma unroll 1
+        for (int kk = 8 * JB; kk < k1; ++kk) {
+            const int kl = kk & 7;
+            const FT c0 = sh.col[lr < R ? a0 : 0];
+            FT c1 = (FT)0;
+            if constexpr (R > 8) c1 = sh.col[lr < R - 8 ? a1 : 0];
+            const bool in0 = at0 >= kk && c0 == c0, in1 = R > 8 && at1 >= kk && c1 == c1;
+            // the largest |c|, ties to the smallest position, NaN never:
+            // code = position * 256 + row
+            const uint32_t code0 = ~(uint32_t)(at0 * 256 + lane);
+            const uint32_t code1 = ~(uint32_t)(at1 * 256 + 64 + lane);
+            uint32_t code;
+            if constexpr (std::is_same<FT, float>::value) {
+                const uint64_t w0 =
+                    ((uint64_t)(__float_as_uint(c0) & 0x7FFFFFFFu) << 32) | code0;
+                const uint64_t w1 =
+                    ((uint64_t)(__float_as_uint(c1) & 0x7FFFFFFFu) << 32) | code1;
+                const uint64_t v0 = in0 ? w0 : 0, v1 = in1 ? w1 : 0;
+                code = (uint32_t)wave_max_u64(v1 > v0 ? v1 : v0);
+            } else {
+                const uint64_t w0 = (uint64_t)__double_as_longlong(fabs(c0)) + 1;
+                const uint64_t w1 = (uint64_t)__double_as_longlong(fabs(c1)) + 1;
+                const uint64_t v0 = in0 ? w0 : 0, v1 = in1 ? w1 : 0;
+                const uint64_t most = wave_max_u64(v1 > v0 ? v1 : v0);
+                const uint32_t e0 = v0 == most && in0 ? code0 : 0;
+                const uint32_t e1 = v1 == most && in1 ? code1 : 0;
+                code = (uint32_t)wave_max_u64(e1 > e0 ? e1 : e0);
+            }
+            if (code == 0) return true;          // no number left: only with a NaN norm
+            const int key = (int)~code;
+            const int row = key & 255, pp = key >> 8;
+            FT pval;
+            if constexpr (std::is_same<FT, float>::value) {
+                pval = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(c0), row & 63));
+                if (R > 8 && row >= 64)
+                    pval = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(c1), row & 63));
+            } else {
+                const uint64_t b0 = (uint64_t)__double_as_longlong(c0);
+                const uint64_t b1 = (uint64_t)__double_as_longlong(c1);
+                uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b0, row & 63);
+                uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b0 >> 32), row & 63);
+                if (R > 8 && row >= 64) {
+                    lo = __builtin_amdgcn_readlane((uint32_t)b1, row & 63);
+                    hi = __builtin_amdgcn_readlane((uint32_t)(b1 >> 32), row & 63);
+                }
+                pval = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+            }
+            if (__builtin_amdgcn_readfirstlane(fabs((double)pval) <= tol ? 1 : 0)) return true;
+            // exchange positions kk and pp
+            if (pp != kk) {
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+                    pos[i] = pos[i] == kk ? pp : (pos[i] == pp ? kk : pos[i]);
+                at0 = at0 == kk ? pp : (at0 == pp ? kk : at0);
+                at1 = at1 == kk ? pp : (at1 == pp ? kk : at1);
+            }
+            // the multipliers, and the pivot row, now at position kk, from its
+            // row of lanes (a test on each slot of each lane: one on the slot
+            // alone put m into indexed memory)
+            if (R >= 8 || lr < R) sh.mul[a0] = c0 / pval;
+            if constexpr (R > 8) {
+                if (lr < R - 8) sh.mul[a1] = c1 / pval;
+            }
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                if (pos[i] == kk) {
+#pragma unroll
+                    for (int j = JB; j <= R; ++j) sh.prow[lq * N::CP + j] = m[i][j];
+                }
+            wave_lds_sync();
+            FT mu[R], pj[R + 1];
+#pragma unroll
+            for (int i = 0; i < R; ++i) mu[i] = sh.mul[lr * N::RP + i];
+#pragma unroll
+            for (int j = JB; j <= R; ++j) pj[j] = sh.prow[lq * N::CP + j];
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                if (pos[i] > kk) {
+                    m[i][JB] = lq > kl ? m[i][JB] - mu[i] * pj[JB] : (lq == kl ? mu[i] : m[i][JB]);
+#pragma unroll
+                    for (int j = JB + 1; j <= R; ++j) m[i][j] -= mu[i] * pj[j];
+                }
+            }
+            // the next column (a choice of values: of stores, it put m into
+            // indexed memory)
+            FT next[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                const FT x0 = m[i][JB], x1 = m[i][JB + 1];
+                next[i] = kl < 7 ? x0 : x1;
+            }
+            if (lq == ((kl + 1) & 7))
+#pragma unroll
+                for (int i = 0; i < R; ++i) sh.col[lr * N::RP + i] = next[i];
+            wave_lds_sync();
+        }
+        return node_eliminate<JB + 1, R, FT>(m, pos, at0, at1, s, lane, tol, sh);
+    } else {
+        return false;
+    }
+}
+
+// Steps 8 JB .. of the forward substitution with L, and all after them (row
+// lr + 8i of m is the row at that position).
+template <int JB, int R, class FT>
+__device__ __forceinline__ void node_forward(FT (&m)[R][R + 1], int s, int lr, int lq) {
+    if constexpr (JB < R) {
+        const int k1 = min(s, 8 * JB + 8);
+#pragma unroll 1
+        for (int kk = 8 * JB; kk < k1; ++kk) {
+            const int kl = kk & 7;
+            FT lv[R];
+#pragma unroll
+            for (int i = JB; i < R; ++i) lv[i] = __shfl(m[i][JB], lr * 8 + kl);
+            const FT wk = __shfl(m[JB][R], kl * 8 + lq);
+            const FT t = m[JB][R] - lv[JB] * wk;
+            m[JB][R] = lr > kl ? t : m[JB][R];
+#pragma unroll
+            for (int i = JB + 1; i < R; ++i) m[i][R] -= lv[i] * wk;
+        }
+        node_forward<JB + 1, R, FT>(m, s, lr, lq);
+    }
+}
+
+// Steps 8 JB + 7 .. 0 of the back substitution: z_kk = w_kk / U(kk, kk), then
+// the rows above remove column kk.
+template <int JB, int R, class FT>
+__device__ __forceinline__ void node_back(FT (&m)[R][R + 1], double (&zr)[R], int s, int lr,
+                                          int lq, bool add) {
+    if constexpr (JB >= 0) {
+#pragma unroll 1
+        for (int kk = min(s, 8 * JB + 8) - 1; kk >= 8 * JB; --kk) {
+            const int kl = kk & 7;
+            FT u[R];
+#pragma unroll
+            for (int i = 0; i <= JB; ++i) u[i] = __shfl(m[i][JB], lr * 8 + kl);
+            const FT zk = __shfl(m[JB][R] / u[JB], kl * 8 + lq);
+            if (lr == kl) zr[JB] = add ? zr[JB] + (double)zk : (double)zk;
+            const FT t = m[JB][R] - u[JB] * zk;
+            m[JB][R] = lr < kl ? t : m[JB][R];
+#pragma unroll
+            for (int i = 0; i < JB; ++i) m[i][R] -= u[i] * zk;
+        }
+        node_back<JB - 1, R, FT>(m, zr, s, lr, lq, add);
+    }
 }
 
 template <int R, bool MIXED, bool GMG>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64, R > 9 ? 1 : 2)
 k_local_node_reg(int32_t nnode, int32_t k, const int32_t *clist, const int32_t *nptr,
                  const int32_t *nbr, const int32_t *rp, const int32_t *cj, const double *v,
                  int32_t *r_cj, double *r_v, int8_t *flags, int32_t *sing, int32_t *nsing,
                  int32_t *bad, int32_t s_lo, int32_t s_hi, double *gslab) {
     using FT = typename std::conditional<MIXED, float, double>::type;
-    constexpr int SC = 8 * R, C = R + 1;
+    constexpr int SC = 8 * R, C = R + 1, HN = NodeReg<R>::HN;
     extern __shared__ double dyn[];
     const int lane = threadIdx.x, lr = lane >> 3, lq = lane & 7;
-    // layout: Mg[s][s] (in this block's global slab when GMG: LDS then
-    // leaves room for more waves per CU), f[k][s] and zs[k][s] (double), two
-    // pivot-row buffers of 8C (FT), ln, off, st, rowat (int)
+    // Mg[s][s], the rows of A(N,N): in this block's global slab when GMG (LDS
+    // then leaves room for more waves per CU)
     double *Mg = GMG ? gslab + (size_t)blockIdx.x * SC * SC : dyn;
-    double *f = GMG ? dyn : dyn + (size_t)SC * SC;
-    double *zs = f + (size_t)k * SC;
-    FT *prow = (FT *)(zs + (size_t)k * SC);
-    int32_t *ln = (int32_t *)(prow + 2 * 8 * C);
-    int32_t *off = ln + SC;
-    int32_t *st = off + SC + 1;
-    int32_t *rowat = st + SC;
+    const NodeShared<R, FT> sh(GMG ? dyn : dyn + (size_t)SC * SC, k);
     for (int64_t node = blockIdx.x; node < nnode; node += gridDim.x) {
         const int32_t c0 = (int32_t)(node * k);
         const int32_t i0 = clist[c0];
         const int32_t n0 = nptr[c0];
-        const int s = nptr[c0 + 1] - n0;
+        const int s = __builtin_amdgcn_readfirstlane(nptr[c0 + 1] - n0);
         if (s < s_lo || s > s_hi) continue;      // outside this launch's size range
         bool ok = s <= SC;
         for (int a = 1; a < k; ++a)
@@ -1869,26 +2091,65 @@ k_local_node_reg(int32_t nnode, int32_t k, const int32_t *clist, const int32_t *
         const int32_t *l = nbr + n0;
         if (lane < k) flags[c0 + lane] = 0;
         __syncthreads();
+        for (int p = lane; p < s; p += 64) {
+            const int32_t r = l[p];
+            sh.ln[p] = r;
+            sh.st[p] = rp[r];
+            sh.en[p] = rp[r + 1];
+        }
         for (int idx = lane; idx < s * s; idx += 64) Mg[idx] = 0.0;
-        for (int idx = lane; idx < k * s; idx += 64) f[idx] = 0.0;
-        for (int p = lane; p < s; p += 64) ln[p] = l[p];
+        for (int idx = lane; idx < k * s; idx += 64) sh.f[idx] = 0.0;
+        for (int idx = lane; idx < HN; idx += 64) sh.hkey[idx] = -1;
         __syncthreads();
-        gather_wave<8, double>(lane, s, ln, off, st, rp, cj, v, Mg, s, nullptr);
-        for (int a = 0; a < k; ++a)
-            for (int e = rp[i0 + a] + lane; e < rp[i0 + a + 1]; e += 64) {
-                int p = bsearch_i32(ln, s, cj[e]);
-                if (p >= 0) f[a * s + p] = -v[e];
+        for (int p = lane; p < s; p += 64) {
+            const int32_t r = sh.ln[p];
+            uint32_t h = sh.slot(r);
+            while (atomicCAS(sh.hkey + h, -1, r) != -1) h = (h + 1) & (HN - 1);
+            sh.hpos[h] = (uint8_t)p;
+        }
+        __syncthreads();
+        // a row of A per row of lanes, eight entries of a lane side by side:
+        // Mg[q][p] = a(l_q, l_p), and right-hand side a: -A(i_a, N)^T
+        for (int q = lr; q < s + k; q += 8) {
+            const bool rhs = q >= s;
+            const int a = rhs ? rp[i0 + q - s] : sh.st[q];
+            const int e = rhs ? rp[i0 + q - s + 1] : sh.en[q];
+            for (int p = a + lq; p < e; p += 64) {
+                int32_t col[8];
+                double val[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int x = min(p + 8 * u, e - 1);
+                    col[u] = cj[x];
+                    val[u] = v[x];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int at = p + 8 * u < e ? sh.place(col[u]) : -1;
+                    if (at >= 0) {
+                        if (rhs) sh.f[(q - s) * s + at] = -val[u];
+                        else Mg[q * s + at] = val[u];
+                    }
+                }
             }
+        }
         __syncthreads();
         double rs = 0.0;
         for (int p = lane; p < s; p += 64) {
             double acc = 0.0;
-            for (int q = 0; q < s; ++q) acc += fabs(Mg[p * s + q]);
+            int q = 0;
+            for (; q + 8 <= s; q += 8) {
+                double d[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) d[u] = Mg[(q + u) * s + p];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc += fabs(d[u]);
+            }
+            for (; q < s; ++q) acc += fabs(Mg[q * s + p]);
             rs = fmax(rs, acc);
         }
         const double tol = SING_TOL * team_max<64>(rs);
         FT m[R][C];
-        FT cur[R];
         int pos[R];
 #pragma unroll
         for (int i = 0; i < R; ++i) {
@@ -1897,92 +2158,16 @@ k_local_node_reg(int32_t nnode, int32_t k, const int32_t *clist, const int32_t *
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const int q = lq + 8 * j;
-                m[i][j] = (r < s && q < s) ? (FT)Mg[r * s + q] : (FT)0;
+                m[i][j] = (r < s && q < s) ? (FT)Mg[q * s + r] : (FT)0;
             }
-            m[i][R] = (r < s && lq < k) ? (FT)f[lq * s + r] : (FT)0;
-            cur[i] = r < s ? (FT)Mg[r * s] : (FT)0;
+            m[i][R] = (r < s && lq < k) ? (FT)sh.f[lq * s + r] : (FT)0;
         }
-        bool singular = false;
+        int at0 = lane < s ? lane : -1, at1 = 64 + lane < s ? 64 + lane : -1;
+        if (lq == 0)
 #pragma unroll
-        for (int jb = 0; jb < R; ++jb) {
-#pragma unroll 1
-            for (int kl = 0; kl < 8; ++kl) {
-                const int kk = 8 * jb + kl;
-                if (kk >= s) break;
-                // arg-max over the unused rows, then across the rows of lanes
-                double pv = -1.0;
-                int key = INT_MAX;
-                FT pval = (FT)0;
-#pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    const double a = fabs((double)cur[i]);
-                    const int ki = pos[i] * 256 + lr + 8 * i;
-                    if (pos[i] >= kk && (a > pv || (a == pv && ki < key))) {
-                        pv = a;
-                        key = ki;
-                        pval = cur[i];
-                    }
-                }
-#pragma unroll
-                for (int o = 8; o < 64; o <<= 1) {
-                    const double ov = __shfl_xor(pv, o);
-                    const int ok2 = __shfl_xor(key, o);
-                    const FT oval = __shfl_xor(pval, o);
-                    if (ov > pv || (ov == pv && ok2 < key)) { pv = ov; key = ok2; pval = oval; }
-                }
-                key = __builtin_amdgcn_readfirstlane(key);
-                // (no candidate at all, key INT_MAX, only with a NaN norm)
-                if (__builtin_amdgcn_readfirstlane(pv <= tol || key == INT_MAX ? 1 : 0)) {
-                    singular = true;
-                    break;
-                }
-                const int pp = key >> 8;
-                // exchange positions kk and pp
-#pragma unroll
-                for (int i = 0; i < R; ++i)
-                    pos[i] = pos[i] == kk ? pp : (pos[i] == pp ? kk : pos[i]);
-                FT mult[R];
-#pragma unroll
-                for (int i = 0; i < R; ++i) mult[i] = cur[i] / pval;
-                // the pivot row through LDS: its row of lanes writes it (the
-                // pivot is the row now at position kk; selecting its slot by
-                // a test on each slot keeps m out of indexed memory)
-                FT *pb = prow + (kk & 1) * 8 * C;
-#pragma unroll
-                for (int i = 0; i < R; ++i)
-                    if (pos[i] == kk) {
-#pragma unroll
-                        for (int j = 0; j < C; ++j)
-                            if (j >= jb) pb[j * 8 + lq] = m[i][j];
-                    }
-                wave_lds_sync();
-                FT pj[C];
-#pragma unroll
-                for (int j = 0; j < C; ++j) pj[j] = j >= jb ? pb[j * 8 + lq] : (FT)0;
-#pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    if (pos[i] > kk) {
-                        const FT mu = mult[i];
-                        m[i][jb] = lq > kl ? m[i][jb] - mu * pj[jb]
-                                           : (lq == kl ? mu : m[i][jb]);
-#pragma unroll
-                        for (int j = 0; j < R; ++j)
-                            if (j > jb) m[i][j] -= mu * pj[j];
-                        m[i][R] = lq < k ? m[i][R] - mu * pj[R] : m[i][R];
-                    }
-                }
-                // the next column along each row of lanes
-                if (kl < 7) {
-#pragma unroll
-                    for (int i = 0; i < R; ++i) cur[i] = __shfl(m[i][jb], lr * 8 + kl + 1);
-                } else if (jb + 1 < R) {
-#pragma unroll
-                    for (int i = 0; i < R; ++i) cur[i] = __shfl(m[i][jb + 1 < R ? jb + 1 : jb], lr * 8);
-                }
-            }
-            if (singular) break;
-        }
-        if (singular) {
+            for (int i = 0; i < R; ++i) sh.col[lr * NodeReg<R>::RP + i] = m[i][0];
+        wave_lds_sync();
+        if (node_eliminate<0, R, FT>(m, pos, at0, at1, s, lane, tol, sh)) {
             if (lane == 0) {
                 const int32_t o = atomicAdd(nsing, k);
                 for (int a = 0; a < k; ++a) {
@@ -1993,111 +2178,84 @@ k_local_node_reg(int32_t nnode, int32_t k, const int32_t *clist, const int32_t *
             __syncthreads();
             continue;
         }
-        // the row at each position, read per step by readlane
-        if (lq == 0) {
+        // the rows in the order of their positions, a column slot at a time
+        if (at0 >= 0) sh.rowat[at0] = lane;
+        if (at1 >= 0) sh.rowat[at1] = 64 + lane;
+        FT *xb = (FT *)sh.z;
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
 #pragma unroll
             for (int i = 0; i < R; ++i)
-                if (pos[i] >= 0) rowat[pos[i]] = lr + 8 * i;
+                if (pos[i] >= 0) xb[pos[i] * 8 + lq] = m[i][j];
+            wave_lds_sync();
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                m[i][j] = lr + 8 * i < s ? xb[i * 64 + lane] : (FT)0;
+            wave_lds_sync();
         }
-        wave_lds_sync();
-        const int ra0 = lane < s ? rowat[lane] : 0;
-        const int ra1 = (SC > 64 && 64 + lane < s) ? rowat[64 + lane] : 0;
         // solution entries q = lr + 8i of right-hand side lq (lanes lq < k)
         double zr[R];
 #pragma unroll
         for (int i = 0; i < R; ++i) zr[i] = 0.0;
+#pragma unroll 1
         for (int pass = 0; pass < (MIXED && s > 0 ? 2 : 1); ++pass) {
             if (pass == 1) {
                 // residual f - M z in double from the gathered matrix, each
-                // entry summed over the columns from the last down; a lane
-                // runs its entries side by side
-                if (lq < k) {
-#pragma unroll
-                    for (int i = 0; i < R; ++i) {
-                        const int q = lr + 8 * i;
-                        if (q < s) zs[lq * s + q] = zr[i];
-                    }
-                }
-                wave_lds_sync();
-                constexpr int NT = (8 * SC + 63) / 64;     // entries per lane, k <= 8
-                const SmallDiv ds(s > 0 ? s : 1);
-                double acc[NT];
-                int bm[NT], bz[NT];
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const int idx = min(lane + 64 * t, k * s - 1);
-                    const int a = ds.quot(idx), p = idx - a * s;
-                    bm[t] = p * s;
-                    bz[t] = a * s;
-                    acc[t] = f[idx];
-                }
-                for (int q = s - 1; q >= 0; --q) {
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) acc[t] -= Mg[bm[t] + q] * zs[bz[t] + q];
-                }
-                wave_lds_sync();
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    if (lane + 64 * t < k * s) f[lane + 64 * t] = acc[t];
-                wave_lds_sync();
-                // the residual as right-hand side (row r takes residual r:
-                // rows never moved), then forward substitution with L
+                // entry summed over the columns from the last down.  A lane
+                // takes a row and every G-th right-hand side: one entry of M
+                // serves them all, read beside its neighbours'
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
-                    const int r = lr + 8 * i;
-                    m[i][R] = (r < s && lq < k) ? (FT)f[lq * s + r] : (FT)0;
+                    const int q = lr + 8 * i;
+                    if (q < s) sh.z[q * 8 + lq] = lq < k ? zr[i] : 0.0;
                 }
+                wave_lds_sync();
+                constexpr int G = SC <= 32 ? 2 : 1, P = 64 / G, U = 8 / G, B = 4;
+                const int g = lane / P;
+                for (int p0 = 0; p0 < s; p0 += P) {
+                    const int p = p0 + lane % P, pc = min(p, s - 1);
+                    double acc[U];
 #pragma unroll
-                for (int jb = 0; jb < R; ++jb) {
-#pragma unroll 1
-                    for (int kl = 0; kl < 8; ++kl) {
-                        const int kk = 8 * jb + kl;
-                        if (kk >= s) break;
-                        const int ph = __builtin_amdgcn_readlane(kk < 64 ? ra0 : ra1, kk & 63);
-                        FT wl = (FT)0;
+                    for (int u = 0; u < U; ++u) acc[u] = sh.f[min(g + G * u, k - 1) * s + pc];
+                    int q = s - 1;
+                    for (; q >= B - 1; q -= B) {
+                        double md[B];
 #pragma unroll
-                        for (int i = 0; i < R; ++i) wl = pos[i] == kk ? m[i][R] : wl;
-                        const FT wk = __shfl(wl, (ph & 7) * 8 + lq);
+                        for (int b = 0; b < B; ++b) md[b] = Mg[(q - b) * s + pc];
 #pragma unroll
-                        for (int i = 0; i < R; ++i) {
-                            const FT lv = __shfl(m[i][jb], lr * 8 + kl);
-                            const FT t = m[i][R] - lv * wk;
-                            m[i][R] = (lq < k && pos[i] > kk) ? t : m[i][R];
-                        }
+                        for (int u = 0; u < U; ++u)
+                            if (G * u < k) {
+#pragma unroll
+                                for (int b = 0; b < B; ++b)
+                                    acc[u] -= md[b] * sh.z[(q - b) * 8 + g + G * u];
+                            }
                     }
+                    for (; q >= 0; --q) {
+                        const double md = Mg[q * s + pc];
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+                            if (G * u < k) acc[u] -= md * sh.z[q * 8 + g + G * u];
+                    }
+                    // (each entry of f is read and written by one lane)
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (p < s && g + G * u < k) sh.f[(g + G * u) * s + p] = acc[u];
                 }
+                wave_lds_sync();
+                // the residual as right-hand side, in the rows' order, then
+                // forward substitution with L
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const int p = lr + 8 * i;
+                    m[i][R] = (p < s && lq < k) ? (FT)sh.f[lq * s + sh.rowat[p]] : (FT)0;
+                }
+                node_forward<0, R, FT>(m, s, lr, lq);
             }
-            // back substitution: z_kk = w(row at kk) / U(kk, kk), then the
-            // rows above remove column kk
-#pragma unroll
-            for (int jb = R - 1; jb >= 0; --jb) {
-#pragma unroll 1
-                for (int kl = 7; kl >= 0; --kl) {
-                    const int kk = 8 * jb + kl;
-                    if (kk >= s) continue;
-                    const int ph = __builtin_amdgcn_readlane(kk < 64 ? ra0 : ra1, kk & 63);
-                    FT ucol[R];
-#pragma unroll
-                    for (int i = 0; i < R; ++i) ucol[i] = __shfl(m[i][jb], lr * 8 + kl);
-                    FT num = (FT)0, den = (FT)1;
-#pragma unroll
-                    for (int i = 0; i < R; ++i) {
-                        num = pos[i] == kk ? m[i][R] : num;
-                        den = pos[i] == kk ? ucol[i] : den;
-                    }
-                    const FT zk = __shfl(num / den, (ph & 7) * 8 + lq);
-                    if (lr == kl) zr[jb] = pass == 0 ? (double)zk : zr[jb] + (double)zk;
-#pragma unroll
-                    for (int i = 0; i < R; ++i) {
-                        const FT t = m[i][R] - ucol[i] * zk;
-                        m[i][R] = (lq < k && pos[i] >= 0 && pos[i] < kk) ? t : m[i][R];
-                    }
-                }
-            }
+            node_back<R - 1, R, FT>(m, zr, s, lr, lq, pass == 1);
         }
         // rows of R: N with the identity entry at the row's place
         int ip = 0;
-        for (int q = lane; q < s; q += 64) ip += (ln[q] < i0) ? 1 : 0;
+        for (int q = lane; q < s; q += 64) ip += (sh.ln[q] < i0) ? 1 : 0;
         ip = team_sum_int<64>(ip);
         if (lq < k) {
 #pragma unroll
@@ -2105,7 +2263,7 @@ k_local_node_reg(int32_t nnode, int32_t k, const int32_t *clist, const int32_t *
                 const int q = lr + 8 * i;
                 if (q < s) {
                     const int64_t o = (int64_t)nptr[c0 + lq] + c0 + lq + q + (q >= ip ? 1 : 0);
-                    r_cj[o] = ln[q];
+                    r_cj[o] = sh.ln[q];
                     r_v[o] = zr[i];
                 }
             }
@@ -2478,19 +2636,20 @@ int64_t local_solves(int32_t nc, const int32_t *clist, const int32_t *nptr,
             rb.add(cost, acc.get(), sizeof(cost));
             rb.run();
         }
-        // Systems up to 72 rows run with M in registers, in three size
-        // classes (the smaller tiles leave more waves per CU); the LDS form
-        // takes the rest.  Its work arrays: in at most 64 KB of LDS (several
-        // blocks per CU) when it takes every system, all of them up to `cap`
-        // rows, all but the double copy of M (MIXED) up to `cap_nomd`; larger
-        // systems use a global slab per block, the grid then kept small
-        // enough for 256 MB of slabs.  When it takes only the few systems
-        // above 72 rows it gets the LDS of a whole CU, which keeps them out
-        // of the slab.  (For the bulk, blocks with the whole LDS of a CU ran
-        // slower: one wave per CU leaves the elimination's latency exposed.)
+        // Systems up to 72 rows (104 in MIXED, whose entries take half the
+        // registers) run with M in registers, in size classes (the smaller
+        // tiles leave more waves per CU); the LDS form takes the rest.  Its
+        // work arrays: in at most 64 KB of LDS (several blocks per CU) when it
+        // takes every system, all of them up to `cap` rows, all but the double
+        // copy of M (MIXED) up to `cap_nomd`; larger systems use a global slab
+        // per block, the grid then kept small enough for 256 MB of slabs.
+        // When it takes only the few systems above the classes it gets the LDS
+        // of a whole CU, which keeps them out of the slab.  (For the bulk,
+        // blocks with the whole LDS of a CU ran slower: one wave per CU leaves
+        // the elimination's latency exposed.)
         const bool reg = knode <= 8 && !env_flag("LAIR_NODE_LDS_SOLVES");
         size_t budget = NODE_LDS_MAX;
-        if (reg && smax > 72) {
+        if (reg && smax > (mixed ? 104 : 72)) {
             const size_t big = mixed ? std::max(node_lds_bytes<float>(smax, knode),
                                                 node_lds_bytes<float>(smax, knode, false))
                                      : node_lds_bytes<double>(smax, knode);
@@ -2538,33 +2697,34 @@ int64_t local_solves(int32_t nc, const int32_t *clist, const int32_t *nptr,
                     LAIR_LAUNCH_CHECK();
                     lo = hi + 1;
                 };
+                // the larger classes keep their double matrix in a global
+                // slab per block (then registers, not LDS, bound the waves
+                // per CU)
+                auto run_slabs = [&](auto kern, int hi, size_t bytes, unsigned most) {
+                    if (lo > smax) return;
+                    const unsigned gs = (unsigned)std::min<int64_t>(nnode, most);
+                    DevArr<double> slabs;
+                    slabs.alloc((size_t)gs * hi * hi, s);
+                    run(kern, hi, bytes, gs, slabs.get());
+                };
                 if (mixed) {
-                    run(k_local_node_reg<3, true, false>, 24, node_reg_lds_bytes<3>(knode), gr,
-                        nullptr);
-                    run(k_local_node_reg<5, true, false>, 40, node_reg_lds_bytes<5>(knode), gr,
-                        nullptr);
-                    if (lo <= smax) {
-                        // the largest class keeps its double matrix in a
-                        // global slab per block (then registers, not LDS,
-                        // bound the waves per CU)
-                        const unsigned g9 = (unsigned)std::min<int64_t>(nnode, 2048);
-                        DevArr<double> slabs;
-                        slabs.alloc((size_t)g9 * 72 * 72, s);
-                        run(k_local_node_reg<9, true, true>, 72,
-                            node_reg_lds_bytes<9>(knode, false), g9, slabs.get());
-                    }
+                    constexpr size_t w = sizeof(float);
+                    run(k_local_node_reg<3, true, false>, 24,
+                        NodeReg<3>::lds_bytes(knode, true, w), gr, nullptr);
+                    run(k_local_node_reg<5, true, false>, 40,
+                        NodeReg<5>::lds_bytes(knode, true, w), gr, nullptr);
+                    run_slabs(k_local_node_reg<9, true, true>, 72,
+                              NodeReg<9>::lds_bytes(knode, false, w), 2048);
+                    run_slabs(k_local_node_reg<13, true, true>, 104,
+                              NodeReg<13>::lds_bytes(knode, false, w), 1024);
                 } else {
-                    run(k_local_node_reg<3, false, false>, 24, node_reg_lds_bytes<3>(knode), gr,
-                        nullptr);
-                    run(k_local_node_reg<5, false, false>, 40, node_reg_lds_bytes<5>(knode), gr,
-                        nullptr);
-                    if (lo <= smax) {
-                        const unsigned g9 = (unsigned)std::min<int64_t>(nnode, 2048);
-                        DevArr<double> slabs;
-                        slabs.alloc((size_t)g9 * 72 * 72, s);
-                        run(k_local_node_reg<9, false, true>, 72,
-                            node_reg_lds_bytes<9>(knode, false), g9, slabs.get());
-                    }
+                    constexpr size_t w = sizeof(double);
+                    run(k_local_node_reg<3, false, false>, 24,
+                        NodeReg<3>::lds_bytes(knode, true, w), gr, nullptr);
+                    run(k_local_node_reg<5, false, false>, 40,
+                        NodeReg<5>::lds_bytes(knode, true, w), gr, nullptr);
+                    run_slabs(k_local_node_reg<9, false, true>, 72,
+                              NodeReg<9>::lds_bytes(knode, false, w), 2048);
                 }
             }
             if (lo <= smax) {
@@ -3891,32 +4051,10 @@ k_dense_lu_lds(int32_t n, double *lu, int32_t *piv, int32_t *info) {
 // leave it scaled in LDS, and after a barrier every thread updates its sixteen
 // entries and column k + 1 is left for the next step.  Arg-max by DPP moves
 // and a ballot instead of shuffles of value and index, and registers instead
-// of an LDS matrix read and written : 46 rows
+// of an LDS matrix read and written each step: 46 rows
 // 103 -> 68 us, 105 rows 299 -> 156 us, 128 rows 441 -> 189 us.
 constexpr int GJ_MAX = 128;
 constexpr int GJ_BS = 1024;
-
-// Largest of a wave's values, in every lane's scalar registers.
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-#define LAIR_DPP_MAX(CTRL)                                                                  \
-    {                                                                                       \
-        const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);                          \
-        const uint32_t l2 = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);     \
-        const uint32_t h2 = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);     \
-        const uint64_t o = ((uint64_t)h2 << 32) | l2;                                       \
-        v = o > v ? o : v;                                                                  \
-    }
-    LAIR_DPP_MAX(0x111)      // row_shr:1
-    LAIR_DPP_MAX(0x112)      // row_shr:2
-    LAIR_DPP_MAX(0x114)      // row_shr:4
-    LAIR_DPP_MAX(0x118)      // row_shr:8
-    LAIR_DPP_MAX(0x142)      // row_bcast:15
-    LAIR_DPP_MAX(0x143)      // row_bcast:31
-#undef LAIR_DPP_MAX
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, 63);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), 63);
-    return ((uint64_t)hi << 32) | lo;
-}
 
 struct GjShared {
     double col[2][GJ_MAX], prow[GJ_MAX];
