@@ -608,9 +608,9 @@ void launch_cf_lists(int32_t n, const int8_t *cf, const int32_t *cidx_scan,
 // ===========================================================================
 // Restriction neighbourhoods N_i (Sec. 3.1; F-F-C paths at distance two,
 // Sec. 4).  One team of T lanes per C-point.  Distance 1 compacts the strong
-// F entries of row i (already sorted).  Distance 2 merges the sorted lists
-// {row i} and {row j : j strong F-neighbour of i}, each filtered to strong
-// F entries; list k belongs to lane k % T, slot k / T (LPL slots per lane).
+// F entries of row i (already sorted).  Distance 2 is the union of {row i}
+// and {row j : j strong F-neighbour of i}, each filtered to strong F entries,
+// in ascending order.
 // ===========================================================================
 constexpr int NBR_LPL = 4;
 
@@ -619,12 +619,13 @@ __device__ __forceinline__ bool nbr_ok(const uint8_t *sm, const int8_t *cf,
     return sm[p] && cf[cj[p]] == 0;
 }
 
+// Distance 1, or every F point.
 template <int T>
 __global__ void k_nbr(int32_t nc, const int32_t *clist, const int32_t *rp,
                       const int32_t *cj, const uint8_t *sm, const int8_t *cf,
                       int32_t distance, const int32_t *flist, int32_t nf,
                       bool fill, int32_t *cnt, const int32_t *nptr,
-                      int32_t *nbr, int32_t *overflow, int32_t knode) {
+                      int32_t *nbr, int32_t knode) {
     // knode > 1 (nodal levels): the knode consecutive C rows of a C-node
     // share their neighbourhood (the strength mask is node-expanded), so one
     // team merges it once, from the node's first row, and writes it for each
@@ -643,40 +644,40 @@ __global__ void k_nbr(int32_t nc, const int32_t *clist, const int32_t *rp,
     }
     int32_t i = clist[c];
     int lo = rp[i], hi = rp[i + 1];
-    if (distance == 1) {
-        int o = 0;
-        for (int p0 = lo; p0 < hi; p0 += T) {
-            int p = p0 + lane;
-            bool q = (p < hi) && nbr_ok(sm, cf, cj, p);
-            uint64_t bits = team_bits<T>(q);
-            int before = __popcll(bits & ((1ull << lane) - 1ull));
-            if (fill && q)
-                for (int32_t a = 0; a < knode; ++a) nbr[nptr[c + a] + o + before] = cj[p];
-            o += __popcll(bits);
-        }
-        if (!fill && lane == 0)
-            for (int32_t a = 0; a < knode; ++a) cnt[c + a] = o;
-        return;
+    int o = 0;
+    for (int p0 = lo; p0 < hi; p0 += T) {
+        int p = p0 + lane;
+        bool q = (p < hi) && nbr_ok(sm, cf, cj, p);
+        uint64_t bits = team_bits<T>(q);
+        int before = __popcll(bits & ((1ull << lane) - 1ull));
+        if (fill && q)
+            for (int32_t a = 0; a < knode; ++a) nbr[nptr[c + a] + o + before] = cj[p];
+        o += __popcll(bits);
     }
-    // distance 2: assign lists to (lane, slot)
+    if (!fill && lane == 0)
+        for (int32_t a = 0; a < knode; ++a) cnt[c + a] = o;
+}
+
+// Distance 2 by merging the sorted lists: list k belongs to lane k % T, slot
+// k / T (NBR_LPL slots per lane).  For the unions too large for the table of
+// k_nbr2; more than T * NBR_LPL lists raise *overflow.
+template <int T>
+__device__ void nbr_merge(int32_t c, int lane, int lo, int hi, const int32_t *rp,
+                          const int32_t *cj, const uint8_t *sm, const int8_t *cf, bool fill,
+                          int32_t *cnt, const int32_t *nptr, int32_t *nbr, int32_t *overflow,
+                          int32_t knode) {
     int pos[NBR_LPL], end[NBR_LPL], head[NBR_LPL];
 #pragma unroll
     for (int m = 0; m < NBR_LPL; ++m) { pos[m] = 0; end[m] = 0; head[m] = INT_MAX; }
     int k = 1;                // list 0 is row i itself
-    bool over = false;
     if (lane == 0) { pos[0] = lo; end[0] = hi; }
     for (int p = lo; p < hi; ++p) {
         if (!nbr_ok(sm, cf, cj, p)) continue;
         if ((k % T) == lane) {
-            int m = k / T;
-            if (m >= NBR_LPL) {
-                over = true;
-            } else {
-                int j = cj[p];
+            const int m = k / T, j = cj[p];
 #pragma unroll
-                for (int mm = 0; mm < NBR_LPL; ++mm)
-                    if (mm == m) { pos[mm] = rp[j]; end[mm] = rp[j + 1]; }
-            }
+            for (int mm = 0; mm < NBR_LPL; ++mm)
+                if (mm == m) { pos[mm] = rp[j]; end[mm] = rp[j + 1]; }
         }
         ++k;
     }
@@ -686,7 +687,6 @@ __global__ void k_nbr(int32_t nc, const int32_t *clist, const int32_t *rp,
             for (int32_t a = 0; a < knode; ++a) cnt[c + a] = 0;
         return;
     }
-    (void)over;
 #pragma unroll
     for (int m = 0; m < NBR_LPL; ++m) {
         while (pos[m] < end[m] && !nbr_ok(sm, cf, cj, pos[m])) ++pos[m];
@@ -719,15 +719,141 @@ __global__ void k_nbr(int32_t nc, const int32_t *clist, const int32_t *rp,
         for (int32_t a = 0; a < knode; ++a) cnt[c + a] = o;
 }
 
+// Distance 2 by a hash set in LDS: every entry of the lists is looked at side
+// by side (eight lanes per list) and enters the team's table and its list of
+// members once; the fill pass writes each member at its rank, the number of
+// smaller members.  What bounds the merge is one round of dependent loads
+// (entry, mask, point type) per member, all lanes waiting: 65536 nodes of up to
+// 18 members 342 + 404 (count + fill) -> 73 + 82 us, 21845 nodes of 72 members
+// 373 + 470 -> 94 + 108 us.  A table of 16 T slots takes 8 T - 1 members; the few
+// larger unions are merged.
+template <int T>
+__global__ void __launch_bounds__(256)
+k_nbr2(int32_t nc, const int32_t *clist, const int32_t *rp, const int32_t *cj,
+       const uint8_t *sm, const int8_t *cf, bool fill, int32_t *cnt, const int32_t *nptr,
+       int32_t *nbr, int32_t *overflow, int32_t knode) {
+    constexpr int H = 16 * T, CAP = 8 * T, HB = 31 - __builtin_clz(H), S = T < 8 ? T : 8, U = 4;
+    __shared__ __align__(16) int32_t s_tab[256 / T][H];
+    __shared__ __align__(16) int32_t s_mem[256 / T][CAP];
+    __shared__ int32_t s_num[256 / T];
+    const int64_t gt = xcd_block_id() * blockDim.x + threadIdx.x;
+    const int32_t c = (int32_t)(gt / T) * knode;
+    const int lane = (int)(gt % T);
+    if (c >= nc) return;
+    int32_t *tab = s_tab[threadIdx.x / T], *mem = s_mem[threadIdx.x / T];
+    int32_t *num = s_num + threadIdx.x / T;
+    // true: col was not in the table before
+    auto insert = [&](int32_t col) {
+        uint32_t h = ((uint32_t)col * 2654435761u) >> (32 - HB);
+        for (;;) {
+            const int32_t x = atomicCAS(tab + h, -1, col);
+            if (x == -1) return true;
+            if (x == col) return false;
+            h = (h + 1) & (H - 1);
+        }
+    };
+    for (int q = lane; q < H; q += T) tab[q] = -1;
+    const int32_t i = clist[c];
+    const int lo = rp[i], hi = rp[i + 1];
+    wave_lds_sync();
+    // row i: its strong F entries are members, and the lists
+    int k = 1, n = 0;
+    bool large = false;
+    for (int p0 = lo; p0 < hi; p0 += T) {
+        if (n + T >= CAP) {
+            large = true;
+            break;
+        }
+        const int p = p0 + lane;
+        const bool ok = p < hi && nbr_ok(sm, cf, cj, p);
+        const int32_t col = ok ? cj[p] : 0;
+        const bool is_new = ok && insert(col);
+        const uint64_t bits = team_bits<T>(is_new);
+        if (is_new) mem[n + __popcll(bits & ((1ull << lane) - 1ull))] = col;
+        n += __popcll(bits);
+        k += __popcll(team_bits<T>(ok));
+    }
+    if (!large && k > T * NBR_LPL) {
+        if (lane == 0) atomicOr(overflow, 1);
+        if (!fill && lane == 0)
+            for (int32_t a = 0; a < knode; ++a) cnt[c + a] = 0;
+        return;
+    }
+    if (lane == 0) *num = n;
+    wave_lds_sync();
+    if (!large) {
+        for (int m = lane / S; m < n; m += T / S) {
+            const int32_t j = mem[m];
+            const int e = rp[j + 1];
+            for (int p0 = rp[j] + lane % S; p0 < e; p0 += S * U) {
+                int32_t col[U];
+                bool ok[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int p = p0 + u * S;
+                    col[u] = p < e ? cj[p] : 0;
+                    ok[u] = p < e && sm[p];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) ok[u] = ok[u] && cf[col[u]] == 0;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    // (a full list stops the team's lanes: at most T more
+                    // than CAP members ever enter the table)
+                    if (ok[u] && *(volatile int32_t *)num < CAP && insert(col[u])) {
+                        const int at = atomicAdd(num, 1);
+                        if (at < CAP) mem[at] = col[u];
+                    }
+            }
+        }
+        wave_lds_sync();
+        n = *num;
+        large = n >= CAP;
+    }
+    if (large) {
+        nbr_merge<T>(c, lane, lo, hi, rp, cj, sm, cf, fill, cnt, nptr, nbr, overflow, knode);
+        return;
+    }
+    if (!fill) {
+        if (lane == 0)
+            for (int32_t a = 0; a < knode; ++a) cnt[c + a] = n;
+        return;
+    }
+    if (lane < 3 && n + lane < CAP) mem[n + lane] = INT_MAX;
+    wave_lds_sync();
+    for (int b = lane; b < n; b += 2 * T) {
+        const int32_t v0 = mem[b], v1 = b + T < n ? mem[b + T] : INT_MAX;
+        int r0 = 0, r1 = 0;
+        for (int q = 0; q < n; q += 4) {
+            const int4 w = *(const int4 *)(mem + q);
+            r0 += (w.x < v0) + (w.y < v0) + (w.z < v0) + (w.w < v0);
+            r1 += (w.x < v1) + (w.y < v1) + (w.z < v1) + (w.w < v1);
+        }
+        for (int32_t a = 0; a < knode; ++a) {
+            const int32_t base = nptr[c + a];
+            nbr[base + r0] = v0;
+            if (b + T < n) nbr[base + r1] = v1;
+        }
+    }
+}
+
 template <int T>
 static void nbr_t(int32_t nc, const int32_t *clist, const int32_t *rp,
                   const int32_t *cj, const uint8_t *sm, const int8_t *cf,
                   int32_t distance, const int32_t *flist, int32_t nf, bool fill,
                   int32_t *cnt, const int32_t *nptr, int32_t *nbr,
                   int32_t *overflow, int32_t knode, hipStream_t s) {
-    LAIR_LAUNCH(k_nbr<T>, dim3(blocks_for((int64_t)(nc / knode) * T, 256)), dim3(256),
-                       0, s, nc, clist, rp, cj, sm, cf, distance, flist, nf, fill,
-                       cnt, nptr, nbr, overflow, knode);
+    const dim3 grid(blocks_for((int64_t)(nc / knode) * T, 256)), blk(256);
+    if constexpr (T >= 4) {
+        if (distance == 2) {
+            LAIR_LAUNCH(k_nbr2<T>, grid, blk, 0, s, nc, clist, rp, cj, sm, cf, fill, cnt, nptr,
+                        nbr, overflow, knode);
+            LAIR_LAUNCH_CHECK();
+            return;
+        }
+    }
+    LAIR_LAUNCH(k_nbr<T>, grid, blk, 0, s, nc, clist, rp, cj, sm, cf, distance, flist, nf, fill,
+                cnt, nptr, nbr, knode);
     LAIR_LAUNCH_CHECK();
 }
 
