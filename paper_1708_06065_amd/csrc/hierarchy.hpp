@@ -128,9 +128,9 @@ struct lair_hierarchy {
     int32_t ss_nblk = 0;
     std::vector<int32_t> sys_levels;
     lair::DevArr<uint8_t> active_dev;
-    // batch solve: the active-row list lengths of every level (3 per level,
-    // at fixed addresses read by captured iterations) followed by the
-    // segment tables of the last list rebuild, uploaded in one copy
+    // batch solve: the active-row list lengths of every level (4 per level,
+    // at fixed addresses read by captured iterations) followed by the runs
+    // that the lists are made of
     lair::DevArr<char> act_upload;
     lair::DevArr<double> seg_norm;
     lair::DevArr<double> e64;

@@ -150,36 +150,67 @@ int32_t relax_list(int32_t nsys, const int64_t *seg, const uint8_t *stopped,
     return (int32_t)cnt;
 }
 
-// All active-row lists of a batch in one launch.  The outputs are laid end
-// to end in one index space; segment j covers [seg_out[j], seg_out[j+1]) of
-// it and copies `len` consecutive entries of list `lst[j]`'s source from
-// seg_src[j] (or the row ids themselves when that list has no source) to
-// its output at seg_dst[j].  No atomics: every position has one writer.
+// All active-row lists of a batch.  List j is made of the runs ptr[j] ..
+// ptr[j + 1] - 1 (system, list, start, length), each a piece of the list's
+// source (or the row ids themselves when it has none); the runs of the active
+// systems follow one another in its output.  No atomics: every position has
+// one writer.
+
+// where each run goes, and the lengths of the lists: one block per list
+constexpr int RUNS_BS = 1024;
+
+__global__ void __launch_bounds__(RUNS_BS)
+k_run_offsets(const int32_t *ptr, const int32_t *sys, const int32_t *len, const uint8_t *active,
+              int32_t *dst, int32_t *cnt) {
+    __shared__ int32_t sums[RUNS_BS / WAVE];
+    const int32_t lo = ptr[blockIdx.x], hi = ptr[blockIdx.x + 1];
+    const int wave = threadIdx.x / WAVE;
+    int32_t before = 0;
+    for (int32_t base = lo; base < hi; base += RUNS_BS) {
+        const int32_t g = base + (int32_t)threadIdx.x;
+        const int32_t v = g < hi && active[sys[g]] ? len[g] : 0;
+        const int32_t incl = team_scan_incl<WAVE>(v);
+        if (threadIdx.x % WAVE == WAVE - 1) sums[wave] = incl;
+        __syncthreads();
+        int32_t at = before + incl - v;
+        for (int w = 0; w < RUNS_BS / WAVE; ++w) {
+            if (w < wave) at += sums[w];
+            before += sums[w];
+        }
+        if (g < hi) dst[g] = at;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) cnt[blockIdx.x] = before;
+}
+
+// one block per run (grid-stride over runs): a straight copy, coalesced
 __global__ void __launch_bounds__(256)
-k_materialize(int32_t nseg, const int64_t *seg_out, const int32_t *seg_src,
-              const int32_t *seg_dst, const int32_t *lst, const int32_t *const *srcs,
-              int32_t *const *dsts) {
-    // one block per segment (grid-stride over segments): a straight copy of
-    // its run, coalesced, with no search per entry
-    for (int32_t g = blockIdx.x; g < nseg; g += gridDim.x) {
-        const int64_t len = seg_out[g + 1] - seg_out[g];
-        const int32_t *src = srcs[lst[g]];
-        int32_t *dst = dsts[lst[g]] + seg_dst[g];
-        const int32_t s0 = seg_src[g];
+k_copy_runs(int32_t nruns, const int32_t *sys, const int32_t *list, const int32_t *start,
+            const int32_t *len, const int32_t *dst, const uint8_t *active,
+            const int32_t *const *srcs, int32_t *const *dsts) {
+    for (int32_t g = blockIdx.x; g < nruns; g += gridDim.x) {
+        if (!active[sys[g]]) continue;
+        const int32_t m = len[g], s0 = start[g];
+        const int32_t *src = srcs[list[g]];
+        int32_t *out = dsts[list[g]] + dst[g];
         if (src) {
-            for (int64_t o = threadIdx.x; o < len; o += blockDim.x) dst[o] = src[s0 + o];
+            for (int32_t o = threadIdx.x; o < m; o += blockDim.x) out[o] = src[s0 + o];
         } else {
-            for (int64_t o = threadIdx.x; o < len; o += blockDim.x) dst[o] = s0 + (int32_t)o;
+            for (int32_t o = threadIdx.x; o < m; o += blockDim.x) out[o] = s0 + o;
         }
     }
 }
 
-void launch_materialize(int32_t nseg, int64_t total, const int64_t *seg_out,
-                        const int32_t *seg_src, const int32_t *seg_dst, const int32_t *lst,
-                        const int32_t *const *srcs, int32_t *const *dsts, hipStream_t s) {
-    if (nseg == 0 || total == 0) return;
-    LAIR_LAUNCH(k_materialize, dim3((unsigned)std::min(nseg, 8192)), dim3(256), 0, s, nseg,
-                seg_out, seg_src, seg_dst, lst, srcs, dsts);
+void launch_active_lists(int32_t nlists, int32_t nruns, const int32_t *ptr, const int32_t *sys,
+                         const int32_t *list, const int32_t *start, const int32_t *len,
+                         int32_t *dst, const uint8_t *active, int32_t *cnt,
+                         const int32_t *const *srcs, int32_t *const *dsts, hipStream_t s) {
+    LAIR_LAUNCH(k_run_offsets, dim3((unsigned)nlists), dim3(RUNS_BS), 0, s, ptr, sys, len, active,
+                dst, cnt);
+    LAIR_LAUNCH_CHECK();
+    if (nruns == 0) return;
+    LAIR_LAUNCH(k_copy_runs, dim3((unsigned)std::min(nruns, 32768)), dim3(256), 0, s, nruns, sys,
+                list, start, len, dst, active, srcs, dsts);
     LAIR_LAUNCH_CHECK();
 }
 

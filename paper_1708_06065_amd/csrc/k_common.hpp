@@ -74,6 +74,18 @@ __device__ __forceinline__ uint64_t team_bits(bool pred) {
     return (b >> first) & mask;
 }
 
+// Inclusive prefix sum over a team of T consecutive lanes.
+template <int T>
+__device__ __forceinline__ int team_scan_incl(int x) {
+    const int p = threadIdx.x % T;
+#pragma unroll
+    for (int o = 1; o < T; o <<= 1) {
+        int u = __shfl_up(x, o, T);
+        if (p >= o) x += u;
+    }
+    return x;
+}
+
 // Arg-max of |value| over a team, ties to the smallest index.
 template <int T>
 __device__ __forceinline__ void team_argmax(double &v, int &idx) {

@@ -1101,18 +1101,6 @@ __device__ __forceinline__ void lane_solve(int32_t c, const int32_t *clist, cons
     r_v[rbase + ip] = 1.0;
 }
 
-// Inclusive prefix sum over a team of T consecutive lanes.
-template <int T>
-__device__ __forceinline__ int team_scan_incl(int x) {
-    const int p = threadIdx.x % T;
-#pragma unroll
-    for (int o = 1; o < T; o <<= 1) {
-        int u = __shfl_up(x, o, T);
-        if (p >= o) x += u;
-    }
-    return x;
-}
-
 // Gathers the local matrix M[k][q] = a(l_q, l_k) (row stride ldm) for the
 // sorted neighbourhood ln[0..s): the entries of the s rows l_q are numbered
 // as one flat range and each lane of the team takes every T-th of them,

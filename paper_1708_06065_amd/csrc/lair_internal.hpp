@@ -569,9 +569,10 @@ void launch_seg_sumsq_blocks(int32_t nsys, int32_t nblk, const int32_t *bsys,
 void launch_block_apply_inv(int32_t nsys, const int64_t *seg, const int64_t *doff,
                             const double *inv, const double *b, double *x, bool transpose,
                             hipStream_t s, const uint8_t *active, const uint8_t *use_inv);
-void launch_materialize(int32_t nseg, int64_t total, const int64_t *seg_out,
-                        const int32_t *seg_src, const int32_t *seg_dst, const int32_t *lst,
-                        const int32_t *const *srcs, int32_t *const *dsts, hipStream_t s);
+void launch_active_lists(int32_t nlists, int32_t nruns, const int32_t *ptr, const int32_t *sys,
+                         const int32_t *list, const int32_t *start, const int32_t *len,
+                         int32_t *dst, const uint8_t *active, int32_t *cnt,
+                         const int32_t *const *srcs, int32_t *const *dsts, hipStream_t s);
 void launch_dense_blocks(int32_t nsys, const int64_t *seg, const int64_t *doff,
                          const int32_t *rp, const int32_t *cj, const double *v,
                          double *dense, int64_t nrows, hipStream_t s);

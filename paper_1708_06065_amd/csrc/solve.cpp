@@ -1212,8 +1212,7 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     if (lists && L0.act_cnt == nullptr) {
         size_t maxseg = 4 * h->L.size() * (size_t)ns;
         for (auto &lp : h->L) maxseg += 4 * (size_t)lp->n / ACT_PIECE;
-        h->act_upload.alloc(cnt_bytes + sizeof(int64_t) * (maxseg + 1) +
-                                3 * sizeof(int32_t) * maxseg + 64, s);
+        h->act_upload.alloc(cnt_bytes + sizeof(int32_t) * (4 * h->L.size() + 1 + 5 * maxseg), s);
         for (size_t l = 0; l < h->L.size(); ++l) {
             Level &Lv = *h->L[l];
             Lv.act_cnt = reinterpret_cast<int32_t *>(h->act_upload.get()) + 4 * l;
@@ -1262,8 +1261,8 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     };
     // rows of the systems still iterated, on every level.  A system's rows,
     // F rows and relaxed C rows are contiguous runs of the level's row range,
-    // F list and relaxed-C list; the host lays out the runs of the active
-    // systems and one kernel copies them (no atomics, fixed order).
+    // F list and relaxed-C list; a kernel lays out the runs of the active
+    // systems and another copies them (no atomics, fixed order).
     std::vector<std::array<std::vector<int32_t>, 3>> runs(nlev);   // per list: prefix over systems
     for (size_t l = 0; lists && l < nlev; ++l) {
         Level &Lv = *h->L[l];
@@ -1295,6 +1294,49 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     if (lists) repack(*h->batch_tail, s);
     const std::vector<int32_t> no_top;
     const std::vector<int32_t> &top = lists ? h->batch_tail->top : no_top;
+    // the runs of every list, laid end to end, as the device holds them:
+    // where each list begins, then each run's system, list, start and length
+    // (long runs in pieces).  When systems stop the host uploads their flags
+    // alone.  (Laid out by the host after every stop: 512 systems, 32 stops, 92
+    // us each before the copy; on the device 7 us.)
+    const int32_t nlists = 4 * (int32_t)nlev;
+    int32_t nruns = 0;
+    std::vector<int32_t> run_tab;
+    int32_t *run_ptr = nullptr, *run_sys = nullptr, *run_list = nullptr, *run_start = nullptr,
+            *run_len = nullptr, *run_dst = nullptr;
+    if (lists) {
+        std::vector<int32_t> ptr{0}, sys, list, start, len;
+        for (size_t l = 0; l < nlev; ++l)
+            for (int t = 0; t < 4; ++t) {
+                const int k = t == 3 ? 0 : t;
+                for (int32_t q = 0; q < ns && (t == 0 || l + 1 < nlev); ++q) {
+                    // a system's tail takes its right-hand side at level
+                    // top[q] and does the rest from there
+                    if ((size_t)top[q] + (t == 0) <= l) continue;
+                    const int32_t m = runs[l][k][q + 1] - runs[l][k][q];
+                    const int32_t s0 = k == 0 ? (int32_t)h->L[l]->seg[q] : runs[l][k][q];
+                    for (int32_t o = 0; o < m; o += ACT_PIECE) {
+                        sys.push_back(q);
+                        list.push_back((int32_t)(4 * l + t));
+                        start.push_back(s0 + o);
+                        len.push_back(std::min(ACT_PIECE, m - o));
+                    }
+                }
+                ptr.push_back((int32_t)sys.size());
+            }
+        nruns = (int32_t)sys.size();
+        run_ptr = reinterpret_cast<int32_t *>(h->act_upload.get() + cnt_bytes);
+        run_sys = run_ptr + nlists + 1;
+        run_list = run_sys + nruns;
+        run_start = run_list + nruns;
+        run_len = run_start + nruns;
+        run_dst = run_len + nruns;
+        run_tab = std::move(ptr);
+        for (const auto *v : {&sys, &list, &start, &len})
+            run_tab.insert(run_tab.end(), v->begin(), v->end());
+        LAIR_HIP(hipMemcpyAsync(run_ptr, run_tab.data(), sizeof(int32_t) * run_tab.size(),
+                                hipMemcpyHostToDevice, s));
+    }
     DevArr<const int32_t *> d_src;
     DevArr<int32_t *> d_dst;
     if (lists) {
@@ -1317,56 +1359,12 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
                                 hipMemcpyHostToDevice, s));
         LAIR_HIP(hipMemcpyAsync(d_dst.get(), dsts.data(), sizeof(void *) * 4 * nlev,
                                 hipMemcpyHostToDevice, s));
-        LAIR_HIP(hipStreamSynchronize(s));     // the pointer tables are pageable host memory
+        LAIR_HIP(hipStreamSynchronize(s));     // the tables are pageable host memory
     }
     auto rebuild_lists = [&]() {
-        std::vector<int64_t> out{0};
-        std::vector<int32_t> src, dst, lst;
-        std::vector<int32_t> counts(4 * nlev, 0);
-        for (size_t l = 0; l < nlev; ++l)
-            for (int t = 0; t < 4; ++t) {
-                if (t > 0 && l + 1 == nlev) continue;
-                int32_t pos = 0;
-                for (int32_t q = 0; q < ns; ++q) {
-                    // a system's tail takes its right-hand side at level
-                    // top[q] and does the rest from there
-                    if (!h->active[q] || (size_t)top[q] + (t == 0) <= l) continue;
-                    const int k = t == 3 ? 0 : t;
-                    const int32_t len = runs[l][k][q + 1] - runs[l][k][q];
-                    if (len == 0) continue;
-                    const int32_t start = k == 0 ? (int32_t)h->L[l]->seg[q] : runs[l][k][q];
-                    // a workgroup copies a run, long ones in pieces
-                    for (int32_t o = 0; o < len; o += ACT_PIECE) {
-                        const int32_t m = std::min(ACT_PIECE, len - o);
-                        out.push_back(out.back() + m);
-                        src.push_back(start + o);
-                        dst.push_back(pos);
-                        lst.push_back((int32_t)(4 * l + t));
-                        pos += m;
-                    }
-                }
-                counts[4 * l + t] = pos;
-            }
-        const int32_t nseg = (int32_t)lst.size();
-        // one pinned upload area with the device layout: the list lengths
-        // (fixed addresses), then the segment offsets, sources, targets and
-        // list numbers; one copy in stream order.  It is rewritten only at
-        // the next rebuild, after the readback that follows this iteration.
-        const size_t b_out = sizeof(int64_t) * out.size(), b_i = sizeof(int32_t) * nseg;
-        const size_t total = cnt_bytes + b_out + 3 * b_i;
-        char *st = (char *)pinned_upload(total + 64);
-        memset(st, 0, cnt_bytes);
-        memcpy(st, counts.data(), sizeof(int32_t) * counts.size());
-        memcpy(st + cnt_bytes, out.data(), b_out);
-        memcpy(st + cnt_bytes + b_out, src.data(), b_i);
-        memcpy(st + cnt_bytes + b_out + b_i, dst.data(), b_i);
-        memcpy(st + cnt_bytes + b_out + 2 * b_i, lst.data(), b_i);
-        char *dev = h->act_upload.get();
-        LAIR_HIP(hipMemcpyAsync(dev, st, total, hipMemcpyHostToDevice, s));
-        const int64_t *d_out = reinterpret_cast<const int64_t *>(dev + cnt_bytes);
-        const int32_t *d_meta = reinterpret_cast<const int32_t *>(dev + cnt_bytes + b_out);
-        launch_materialize(nseg, out.back(), d_out, d_meta, d_meta + nseg, d_meta + 2 * nseg,
-                           d_src.get(), d_dst.get(), s);
+        launch_active_lists(nlists, nruns, run_ptr, run_sys, run_list, run_start, run_len,
+                            run_dst, h->active_dev.get(), L0.act_cnt, d_src.get(), d_dst.get(),
+                            s);
     };
     struct ActGuard {
         lair_hierarchy *h;
@@ -1416,7 +1414,10 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
         hist.push_back(*std::max_element(rel.begin(), rel.end()));
         if (nact == 0 || it >= maxit) break;
         if (upload) {
-            LAIR_HIP(hipMemcpyAsync(h->active_dev.get(), h->active.data(), (size_t)ns,
+            // (the pinned area is free: a readback has followed its last use)
+            void *st = pinned_upload((size_t)ns);
+            memcpy(st, h->active.data(), (size_t)ns);
+            LAIR_HIP(hipMemcpyAsync(h->active_dev.get(), st, (size_t)ns,
                                     hipMemcpyHostToDevice, s));
             if (lists) rebuild_lists();
             upload = false;
