@@ -429,6 +429,9 @@ static const int32_t MAX_DENSE = 4096;
 // ---------------------------------------------------------------------------
 // Setup
 // ---------------------------------------------------------------------------
+// Host bytes of a level's pattern that a splitting on the host keeps pinned.
+constexpr size_t SPLIT_PINNED_MAX = (size_t)16 << 20;
+
 // Strength, splitting, neighbourhoods, local solves, R and P of one level,
 // and the product counts of A P (left in ap for the caller's product).
 // Host synchronisations: the number of C-points with the F/C row lists,
@@ -514,13 +517,28 @@ static void build_level_transfer(lair_hierarchy *h, Level &Lv, int32_t lvl,
                                 h->str.kind, smc.get(), mean, s);
             sm_dev = smc.get();
         }
-        std::vector<int32_t> hrp((size_t)n + 1), hcj((size_t)A.nnz);
-        std::vector<uint8_t> hsm((size_t)A.nnz);
-        std::vector<int8_t> hcf((size_t)n);
-        LAIR_HIP(hipMemcpyAsync(hrp.data(), A.rp.get(), sizeof(int32_t) * (n + 1), hipMemcpyDeviceToHost, s));
+        // copied into this thread's pinned area (and back from the one for
+        // uploads, which the readbacks below follow) when it is not too large
+        // to keep; through pageable memory the three copies of a 97 x 97
+        // grid's levels took 0.1 ms each
+        const size_t b_rp = (sizeof(int32_t) * ((size_t)n + 1) + 15) & ~(size_t)15;
+        const size_t b_cj = (sizeof(int32_t) * (size_t)A.nnz + 15) & ~(size_t)15;
+        const size_t b_all = b_rp + b_cj + (size_t)A.nnz;
+        const bool pin = b_all <= SPLIT_PINNED_MAX;
+        std::unique_ptr<char[]> pageable, pageable_cf;
+        if (!pin) {
+            pageable.reset(new char[b_all]);
+            pageable_cf.reset(new char[(size_t)n]);
+        }
+        char *host = pin ? (char *)pinned_staging(b_all) : pageable.get();
+        int32_t *hrp = reinterpret_cast<int32_t *>(host);
+        int32_t *hcj = reinterpret_cast<int32_t *>(host + b_rp);
+        uint8_t *hsm = reinterpret_cast<uint8_t *>(host + b_rp + b_cj);
+        int8_t *hcf = reinterpret_cast<int8_t *>(pin ? pinned_upload((size_t)n) : pageable_cf.get());
+        LAIR_HIP(hipMemcpyAsync(hrp, A.rp.get(), sizeof(int32_t) * (n + 1), hipMemcpyDeviceToHost, s));
         if (A.nnz) {
-            LAIR_HIP(hipMemcpyAsync(hcj.data(), A.cj.get(), sizeof(int32_t) * A.nnz, hipMemcpyDeviceToHost, s));
-            LAIR_HIP(hipMemcpyAsync(hsm.data(), sm_dev, (size_t)A.nnz, hipMemcpyDeviceToHost, s));
+            LAIR_HIP(hipMemcpyAsync(hcj, A.cj.get(), sizeof(int32_t) * A.nnz, hipMemcpyDeviceToHost, s));
+            LAIR_HIP(hipMemcpyAsync(hsm, sm_dev, (size_t)A.nnz, hipMemcpyDeviceToHost, s));
         }
         LAIR_HIP(hipStreamSynchronize(s));
         if (nod) {
@@ -542,10 +560,10 @@ static void build_level_transfer(lair_hierarchy *h, Level &Lv, int32_t lvl,
             rs_first_pass(nn, nrp.data(), ncj.data(), nsm.data(), ncf.data());
             for (int32_t r = 0; r < n; ++r) hcf[r] = ncf[r / kb];
         } else {
-            rs_first_pass(n, hrp.data(), hcj.data(), hsm.data(), hcf.data());
+            rs_first_pass(n, hrp, hcj, hsm, hcf);
         }
-        LAIR_HIP(hipMemcpyAsync(Lv.cf.get(), hcf.data(), (size_t)n, hipMemcpyHostToDevice, s));
-        LAIR_HIP(hipStreamSynchronize(s));
+        LAIR_HIP(hipMemcpyAsync(Lv.cf.get(), hcf, (size_t)n, hipMemcpyHostToDevice, s));
+        if (!pin) LAIR_HIP(hipStreamSynchronize(s));
         h->split_ms += ms_since(t_split);
     }
     std::vector<int64_t> seg_next;
