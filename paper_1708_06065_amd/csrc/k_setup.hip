@@ -3139,6 +3139,114 @@ k_interp_direct(int32_t n, const int32_t *rp, const int32_t *cj,
     interp_direct_write<T>(i, lo, hi, lane, cj, v, sm, cf, cidx, prp[i], alpha, beta, d, pcj, pv);
 }
 
+// The same with a lane per row, T <= 8 the team it stands for: entry p of the
+// row goes to accumulator (p - lo) % T, and the accumulators are added in the
+// order of the team's reduction, so every weight has the same bits.  Teams of
+// 8 lanes spend their time on instructions (shuffles of five sums and
+// divisions for 8 rows a wave, not 64).
+template <int T>
+__global__ void __launch_bounds__(256)
+k_interp_direct_lane(int32_t n, const int32_t *rp, const int32_t *cj, const double *v,
+                     const uint8_t *sm, const int8_t *cf, const int32_t *cidx, bool fill,
+                     int32_t *cnt, const int32_t *prp, int32_t *pcj, double *pv, double *coef) {
+    const int32_t i = (int32_t)(xcd_block_id() * blockDim.x + threadIdx.x);
+    if (i >= n) return;
+    const int lo = rp[i], hi = rp[i + 1];
+    int o = fill ? prp[i] : 0;
+    if (cf[i] == 1) {
+        if (!fill) cnt[i] = 1;
+        else { pcj[o] = cidx[i]; pv[o] = 1.0; }
+        return;
+    }
+    double alpha, beta, d;
+    bool empty;
+    if (fill && coef) {
+        // the sizing pass kept alpha, beta and the lumped diagonal (0: no row)
+        alpha = coef[3 * (int64_t)i];
+        beta = coef[3 * (int64_t)i + 1];
+        d = coef[3 * (int64_t)i + 2];
+        empty = d == 0.0;
+    } else {
+        double diag = 0.0, sn[T], sp[T], pn[T], pp[T];
+        int k = 0;
+#pragma unroll
+        for (int u = 0; u < T; ++u) sn[u] = sp[u] = pn[u] = pp[u] = 0.0;
+        for (int p0 = lo; p0 < hi; p0 += T) {
+            int j[T];
+            double a[T];
+            bool st[T];
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                const bool in = p0 + u < hi;
+                j[u] = in ? cj[p0 + u] : -1;
+                a[u] = in ? v[p0 + u] : 0.0;
+                st[u] = in && sm[p0 + u];
+            }
+#pragma unroll
+            for (int u = 0; u < T; ++u) st[u] = st[u] && j[u] != i && cf[j[u]] == 1;
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                if (j[u] == i) {
+                    diag = a[u];
+                } else if (j[u] >= 0) {
+                    const bool neg = a[u] < 0.0;
+                    sn[u] += neg ? a[u] : 0.0;
+                    sp[u] += neg ? 0.0 : a[u];
+                    pn[u] += st[u] && neg ? a[u] : 0.0;
+                    pp[u] += st[u] && !neg ? a[u] : 0.0;
+                    k += st[u];
+                }
+            }
+        }
+#pragma unroll
+        for (int w = T / 2; w > 0; w >>= 1)
+#pragma unroll
+            for (int u = 0; u < w; ++u) {
+                sn[u] += sn[u + w];
+                sp[u] += sp[u + w];
+                pn[u] += pn[u + w];
+                pp[u] += pp[u + w];
+            }
+        d = diag;
+        if (pn[0] == 0.0) d += sn[0];
+        if (pp[0] == 0.0) d += sp[0];
+        empty = k == 0 || d == 0.0;
+        alpha = pn[0] != 0.0 ? sn[0] / pn[0] : 0.0;
+        beta = pp[0] != 0.0 ? sp[0] / pp[0] : 0.0;
+        if (!fill) {
+            cnt[i] = empty ? 0 : k;
+            if (coef) {
+                coef[3 * (int64_t)i] = alpha;
+                coef[3 * (int64_t)i + 1] = beta;
+                coef[3 * (int64_t)i + 2] = empty ? 0.0 : d;
+            }
+            return;
+        }
+    }
+    if (empty) return;
+    for (int p0 = lo; p0 < hi; p0 += T) {
+        int j[T];
+        double a[T];
+        bool st[T];
+#pragma unroll
+        for (int u = 0; u < T; ++u) {
+            const bool in = p0 + u < hi;
+            j[u] = in ? cj[p0 + u] : -1;
+            a[u] = in ? v[p0 + u] : 0.0;
+            st[u] = in && sm[p0 + u];
+        }
+#pragma unroll
+        for (int u = 0; u < T; ++u) st[u] = st[u] && j[u] != i && cf[j[u]] == 1;
+#pragma unroll
+        for (int u = 0; u < T; ++u)
+            if (st[u]) {
+                pcj[o] = cidx[j[u]];
+                pv[o] = -(a[u] < 0.0 ? alpha : beta) * a[u] / d;
+                ++o;
+            }
+    }
+}
+
 void launch_interp_direct(int32_t n, const int32_t *rp, const int32_t *cj,
                           const double *v, const uint8_t *smask,
                           const int8_t *cf, const int32_t *cidx, bool fill,
@@ -3146,15 +3254,27 @@ void launch_interp_direct(int32_t n, const int32_t *rp, const int32_t *cj,
                           double *pv, double mean_len, hipStream_t s, double *coef) {
     int t = team_for_mean(mean_len);
     if (t > 16) t = 16;
-#define LAIR_ID(TT)                                                              \
-    LAIR_LAUNCH(k_interp_direct<TT>, dim3(blocks_for((int64_t)n * TT, 256)), \
-                       dim3(256), 0, s, n, rp, cj, v, smask, cf, cidx, fill, cnt, prp, \
-                       pcj, pv, coef)
+    // a lane per row fills the chip from about 2^18 rows on; below, its rows'
+    // serial work shows (44800 rows 5 us by teams, 15 by lanes; 512000 rows 29
+    // and 23; 10.6 million 647 and 295, the fill 781 and 367)
+    const bool lanes = t <= 8 && n >= (1 << 18);
+#define LAIR_ID(TT, KERN, LANES)                                                        \
+    LAIR_LAUNCH(KERN<TT>, dim3(blocks_for((int64_t)n * LANES, 256)), dim3(256), 0, s, n, rp, cj, \
+                v, smask, cf, cidx, fill, cnt, prp, pcj, pv, coef)
+    if (lanes) {
+        switch (t) {
+            case 2: LAIR_ID(2, k_interp_direct_lane, 1); break;
+            case 4: LAIR_ID(4, k_interp_direct_lane, 1); break;
+            default: LAIR_ID(8, k_interp_direct_lane, 1); break;
+        }
+        LAIR_LAUNCH_CHECK();
+        return;
+    }
     switch (t) {
-        case 2: LAIR_ID(2); break;
-        case 4: LAIR_ID(4); break;
-        case 8: LAIR_ID(8); break;
-        default: LAIR_ID(16); break;
+        case 2: LAIR_ID(2, k_interp_direct, 2); break;
+        case 4: LAIR_ID(4, k_interp_direct, 4); break;
+        case 8: LAIR_ID(8, k_interp_direct, 8); break;
+        default: LAIR_ID(16, k_interp_direct, 16); break;
     }
 #undef LAIR_ID
     LAIR_LAUNCH_CHECK();
