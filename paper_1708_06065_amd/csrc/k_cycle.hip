@@ -812,14 +812,12 @@ void op_jacobi(const CsrView<VT> &A, const int32_t *rows, int32_t nx,
 
 template <class VT>
 __global__ void k_scatter(int64_t total, int32_t nrhs, const int32_t *rows, int32_t row0,
-                          const int32_t *cnt, const VT *t, VT *x) {
-    const int64_t n = cnt ? (int64_t)*cnt * nrhs : total;
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n;
-         g += (int64_t)gridDim.x * blockDim.x) {
-        int64_t k = g / nrhs;
-        int q = (int)(g % nrhs);
-        x[(int64_t)list_row(rows, row0, k) * nrhs + q] = t[g];
-    }
+                          const VT *t, VT *x) {
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= total) return;
+    const int64_t k = g / nrhs;
+    const int q = (int)(g % nrhs);
+    x[(int64_t)list_row(rows, row0, k) * nrhs + q] = t[g];
 }
 
 // A contiguous row range: a straight copy, 16 bytes per thread.
@@ -830,9 +828,8 @@ __global__ void k_copy16(int64_t n16, const int4 *src, int4 *dst) {
 
 template <class VT>
 void op_scatter(const int32_t *rows, int32_t nx, const VT *t, VT *x,
-                int32_t nrhs, hipStream_t s, const int32_t *cnt, int32_t row0) {
+                int32_t nrhs, hipStream_t s, int32_t row0) {
     if (nx == 0) return;
-    if (!rows && cnt) fail(LAIR_EINVAL, "a counted row list needs its rows");
     int64_t total = (int64_t)nx * nrhs;
     VT *dst = x + (int64_t)row0 * nrhs;
     if (!rows && (total * (int64_t)sizeof(VT)) % 16 == 0 && aligned16(t) && aligned16(dst)) {
@@ -842,8 +839,8 @@ void op_scatter(const int32_t *rows, int32_t nx, const VT *t, VT *x,
         LAIR_LAUNCH_CHECK();
         return;
     }
-    LAIR_LAUNCH((k_scatter<VT>), dim3(cnt ? list_grid(total) : blocks_for(total, 256)),
-                dim3(256), 0, s, total, nrhs, rows, row0, cnt, t, x);
+    LAIR_LAUNCH((k_scatter<VT>), dim3(blocks_for(total, 256)), dim3(256), 0, s, total, nrhs,
+                rows, row0, t, x);
     LAIR_LAUNCH_CHECK();
 }
 
@@ -1316,8 +1313,8 @@ template void op_update_list<double>(const int32_t *, const int32_t *, int32_t, 
 template void op_update_list<float>(const int32_t *, const int32_t *, int32_t, double *, const float *, hipStream_t);
 template void op_coarse_apply<double>(int32_t, const double *, const double *, double *, int32_t, bool, hipStream_t);
 template void op_coarse_apply<float>(int32_t, const double *, const float *, float *, int32_t, bool, hipStream_t);
-template void op_scatter<double>(const int32_t *, int32_t, const double *, double *, int32_t, hipStream_t, const int32_t *, int32_t);
-template void op_scatter<float>(const int32_t *, int32_t, const float *, float *, int32_t, hipStream_t, const int32_t *, int32_t);
+template void op_scatter<double>(const int32_t *, int32_t, const double *, double *, int32_t, hipStream_t, int32_t);
+template void op_scatter<float>(const int32_t *, int32_t, const float *, float *, int32_t, hipStream_t, int32_t);
 template void op_fill<double>(double *, double, int64_t, hipStream_t);
 template void op_fill<float>(float *, float, int64_t, hipStream_t);
 template void op_copy<double>(const double *, double *, int64_t, hipStream_t);

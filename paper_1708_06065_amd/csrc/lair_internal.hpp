@@ -452,8 +452,7 @@ void op_coarse_apply(int32_t n, const double *kinv, const VT *b, VT *x,
                      int32_t nrhs, bool transpose, hipStream_t s);
 template <class VT>
 void op_scatter(const int32_t *rows, int32_t nrows, const VT *t, VT *x,
-                int32_t nrhs, hipStream_t s, const int32_t *cnt = nullptr,
-                int32_t row0 = 0);
+                int32_t nrhs, hipStream_t s, int32_t row0 = 0);
 template <class VT>
 void op_fill(VT *x, VT val, int64_t n, hipStream_t s);
 template <class VT>

@@ -180,7 +180,7 @@ static bool ffc(lair_hierarchy *h, Level &Lv, const VT *b, VT *x, int32_t nrhs,
     if (leave_c) return true;
     {
         ProfScope ps("scatter", s, 4.0 * ncr + 2.0 * w * nrhs * ncr);
-        op_scatter<VT>(crows, ncr, y, x, nrhs, s, nullptr, c0);
+        op_scatter<VT>(crows, ncr, y, x, nrhs, s, c0);
     }
     return false;
 }

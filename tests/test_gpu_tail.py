@@ -135,8 +135,9 @@ def test_batch_workgroups_equal_launches(lair, sizes, kw, precision):
     prof = lair.profile_end()
     assert prof["tail"]["launches"] == 1
     assert torch.isfinite(x).all() and torch.equal(launched, x)
-    again, _ = h.solve_batch(b, maxit=1)          # captured iterations
-    assert torch.equal(x, again)
+    for _ in range(30):           # the last of them replay a captured iteration
+        again, _ = h.solve_batch(b, maxit=1)
+        assert torch.equal(x, again)
     h.free()
 
 
