@@ -1962,8 +1962,9 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
 // two waves per SIMD (the registers of the largest classes).  The matrix is
 // gathered as the rows of A, so that a wave reads a column of M side by side;
 // a hash of N finds a column's place in one or two reads where a search took
-// seven; blocks of eight steps are instances of templates, since as a loop
-// unrolled by pragma the compiler kept m of the largest class in scratch.
+// seven; blocks of eight steps are instances of templates (one loop over the
+// column slots unrolled by pragma is past the compiler's size limit in the
+// largest classes, and m then goes to scratch memory).
 // 21843 systems of 72 rows with 6 right-hand sides, mixed: 4.55 -> 2.23 ms;
 // 65536 of 12 and 18 rows 0.98 -> 0.58 ms; a launch with a few of up to 72 rows
 // 0.41 -> 0.18 ms, of up to 104 rows (in LDS before) 0.7 to 1.5 -> 0.26 to 0.56 ms.
@@ -4223,56 +4224,6 @@ k_dense_lu(int32_t n, double *a, int32_t *piv, int32_t *info) {
     if (t == 0) *info = 0;
 }
 
-// Small coarsest grids (n <= 128): the whole factorisation in LDS, pivot
-// search by the first wave with shuffles (largest |a|, smallest row on ties).
-__global__ void __launch_bounds__(256)
-k_dense_lu_lds(int32_t n, double *lu, int32_t *piv, int32_t *info) {
-    extern __shared__ double a[];
-    __shared__ int s_piv;
-    __shared__ double s_val;
-    int t = threadIdx.x, nt = blockDim.x;
-    for (int idx = t; idx < n * n; idx += nt) a[idx] = lu[idx];
-    __syncthreads();
-    for (int k = 0; k < n; ++k) {
-        if (t < 64) {
-            double best = -1.0;
-            int bi = INT_MAX;
-            for (int r = k + t; r < n; r += 64) {
-                double x = fabs(a[r * n + k]);
-                if (x > best) { best = x; bi = r; }
-            }
-            team_argmax<64>(best, bi);
-            if (t == 0) { s_piv = bi; s_val = best; }
-        }
-        __syncthreads();
-        int pr = s_piv;
-        if (s_val == 0.0) {
-            if (t == 0) *info = k + 1;
-            return;
-        }
-        if (t == 0) piv[k] = pr;
-        if (pr != k)
-            for (int q = t; q < n; q += nt) {
-                double x = a[k * n + q];
-                a[k * n + q] = a[pr * n + q];
-                a[pr * n + q] = x;
-            }
-        __syncthreads();
-        double inv = 1.0 / a[k * n + k];
-        for (int r = k + 1 + t; r < n; r += nt) a[r * n + k] *= inv;
-        __syncthreads();
-        int w = n - k - 1;
-        for (int idx = t; idx < w * w; idx += nt) {
-            int r = k + 1 + idx / w;
-            int q = k + 1 + idx % w;
-            a[r * n + q] -= a[r * n + k] * a[k * n + q];
-        }
-        __syncthreads();
-    }
-    for (int idx = t; idx < n * n; idx += nt) lu[idx] = a[idx];
-    if (t == 0) *info = 0;
-}
-
 // Coarsest grids of up to 128 rows: the explicit inverse by Gauss-Jordan
 // elimination in place with partial pivoting, one workgroup per grid, the
 // matrix in registers.  Thread (ty, tx) of 32 x 32 holds rows ty + 32 i and
@@ -4438,12 +4389,6 @@ bool launch_dense_gj_inv(int32_t n, const double *dense, double *inv, int32_t *i
 
 void launch_dense_lu(int32_t n, double *lu, int32_t *piv, int32_t *info,
                      hipStream_t s) {
-    if (n <= 128 && (size_t)n * n * sizeof(double) + 64 <= max_lds_per_block()) {
-        LAIR_LAUNCH(k_dense_lu_lds, dim3(1), dim3(256), (size_t)n * n * sizeof(double),
-                           s, n, lu, piv, info);
-        LAIR_LAUNCH_CHECK();
-        return;
-    }
     int bs = 64;
     while (bs < 1024 && bs < n) bs <<= 1;
     LAIR_LAUNCH(k_dense_lu, dim3(1), dim3(bs), 0, s, n, lu, piv, info);
