@@ -2804,8 +2804,15 @@ int64_t local_solves(int32_t nc, const int32_t *clist, const int32_t *nptr,
             const unsigned gr = (unsigned)std::min<int64_t>(nnode, 8192);
             int lo = 0;
             if (reg) {
+                // Up to 1024 nodes every node has a SIMD of its own even in the
+                // largest class, and a launch takes as long as its largest
+                // node: one class then takes them all (730 nodes of up to 102
+                // rows: 374 us against four launches of 62, 94, 200 and 381; with
+                // 2252 nodes the four take 62, 98, 330 and 563)
+                const int top = std::min(smax, mixed ? 104 : 72);
+                const bool one = nnode <= 1024;
                 auto run = [&](auto kern, int hi, size_t bytes, unsigned grid, double *slabs) {
-                    if (lo > smax) return;
+                    if (lo > smax || (one && hi < top)) return;
                     LAIR_LAUNCH(kern, dim3(grid), dim3(64), bytes, s, nnode, knode, clist, nptr,
                                 nbr, rp, cj, v, out.r_cj, out.r_v, out.flags, sing.get(),
                                 cnt + 6, cnt, lo, hi, slabs);
@@ -2816,7 +2823,7 @@ int64_t local_solves(int32_t nc, const int32_t *clist, const int32_t *nptr,
                 // slab per block (then registers, not LDS, bound the waves
                 // per CU)
                 auto run_slabs = [&](auto kern, int hi, size_t bytes, unsigned most) {
-                    if (lo > smax) return;
+                    if (lo > smax || (one && hi < top)) return;
                     const unsigned gs = (unsigned)std::min<int64_t>(nnode, most);
                     DevArr<double> slabs;
                     slabs.alloc((size_t)gs * hi * hi, s);

@@ -1,5 +1,6 @@
 """GPU: the node solves at the edges of their size classes (24, 40, 72 and 104
-rows): the rows of R are those of separate solves of the scalar rows, bit for
+rows), with so few nodes that one class takes them all and with more (above
+1024): the rows of R are those of separate solves of the scalar rows, bit for
 bit, as every entry sees the same operations in the same order."""
 import numpy as np
 import pytest
@@ -34,11 +35,16 @@ def _stars(k, sizes, seed):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
-@pytest.mark.parametrize("k", [2, 3, 8])
-def test_size_classes(lair, monkeypatch, k, precision):
-    print("case: node sizes", k, precision, flush=True)
-    edges = [24, 40, 72, 104, 64, 128]
-    sizes = sorted({0, 1} | {max(0, e // k + d) for e in edges for d in (-1, 0, 1)})
+@pytest.mark.parametrize("k,more,largest",
+                         [(k, 0, m) for k in (2, 3, 8) for m in (24, 40, 72, 104, 128)] +
+                         [(2, 1025, 40), (2, 1025, 128)])
+def test_size_classes(lair, monkeypatch, k, more, largest, precision):
+    print("case: node sizes", k, more, largest, precision, flush=True)
+    edges = [e for e in (24, 40, 64, 72, 104, 128) if e <= largest]
+    sizes = sorted({0, 1} | {max(0, e // k + d) for e in edges for d in (-1, 0, 1)
+                             if k * (e // k + d) <= largest})
+    if more:
+        sizes += [1] * (more - len(sizes))
     A, cf = _stars(k, sizes, k)
     R = {}
     for mode in ("rows", "nodes"):
