@@ -375,6 +375,14 @@ static Tail *find_tail(lair_hierarchy *h, int32_t nrhs, bool transpose, size_t l
     return nullptr;
 }
 
+// Work queued on s would only be recorded (also when that cannot be told).
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) return false;
+    (void)hipGetLastError();
+    return true;
+}
+
 // Make the tail of a cycle kind, or pack it again after new values.  Not while
 // the stream is captured: the cycle then runs launch by launch, the same sums.
 static void ensure_tail(lair_hierarchy *h, int32_t nrhs, bool mixed, bool transpose,
@@ -384,11 +392,7 @@ static void ensure_tail(lair_hierarchy *h, int32_t nrhs, bool mixed, bool transp
     for (auto &t : h->tails)
         if (t.w == w && t.nrhs == nrhs && t.transpose == transpose) have = &t;
     if (have && !have->stale) return;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return;
-    }
+    if (capturing(s)) return;
     if (have) {
         repack(*have, s);
         return;
@@ -637,7 +641,16 @@ static void ensure_transposes(lair_hierarchy *h, hipStream_t cs) {
     if (h->have_transpose && !h->transpose_stale) return;
     const size_t nl = h->L.size();
     if (h->have_transpose) {
-        // new values on the kept patterns
+        // new values on the kept patterns; under capture at once, on the
+        // stream of the new diagonal: recorded, they would be missing from
+        // every call before the graph's first replay
+        const bool aside = capturing(cs);
+        if (aside) {
+            cs = h->stream;
+            if (capturing(cs))
+                fail(LAIR_EDEVICE, "the transposed operators of a new diagonal cannot be made "
+                     "while its stream is captured");
+        }
         TransposeValues t{};
         int m = 0;
         auto add = [&](const DevCSR &M, DevCSR &T, const DevArr<int32_t> &pos) {
@@ -656,6 +669,7 @@ static void ensure_transposes(lair_hierarchy *h, hipStream_t cs) {
             launch_diagonal(Lv.n, Lv.A.rp.get(), Lv.A.cj.get(), Lv.A.v.get(), Lv.tdiag.get(), cs);
         }
         if (m) launch_transpose_values(t, m, cs);
+        if (aside) LAIR_HIP(hipStreamSynchronize(cs));
         h->transpose_stale = false;
         return;
     }
