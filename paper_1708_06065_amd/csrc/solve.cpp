@@ -375,6 +375,18 @@ static Tail *find_tail(lair_hierarchy *h, int32_t nrhs, bool transpose, size_t l
     return nullptr;
 }
 
+// What make() returns, or nothing when there is no memory for it: the cycle
+// runs without a tail, so a call that fits without one does not fail for it.
+template <class Make>
+static auto unless_no_memory(Make &&make) -> decltype(make()) {
+    try {
+        return make();
+    } catch (const Error &e) {
+        if (e.status != LAIR_ENOMEM) throw;
+        return {};
+    }
+}
+
 // Work queued on s would only be recorded (also when that cannot be told).
 static bool capturing(hipStream_t s) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -400,8 +412,10 @@ static void ensure_tail(lair_hierarchy *h, int32_t nrhs, bool mixed, bool transp
     const size_t start = tail_start(h, w, transpose);
     Tail T;
     if (start < h->L.size())
-        T = mixed ? make_tail<float>(h, start, nrhs, transpose, s)
-                  : make_tail<double>(h, start, nrhs, transpose, s);
+        T = unless_no_memory([&] {
+            return mixed ? make_tail<float>(h, start, nrhs, transpose, s)
+                         : make_tail<double>(h, start, nrhs, transpose, s);
+        });
     T.w = w;
     T.nrhs = nrhs;
     T.transpose = transpose;
@@ -551,11 +565,11 @@ static std::unique_ptr<Tail> make_batch_tail(lair_hierarchy *h,
         T->flops += share * 2.0 * ((double)Lv.R.nnz + Lv.P.nnz + 2.0 * Lv.nnzF + Lv.nnzC);
     }
     if (total > TAIL_MAX_BATCH_PACK) return nullptr;
+    T->blob.alloc(std::max<size_t>(total, 256), s);
     int32_t *st = (int32_t *)pinned_upload(sizeof(int32_t) * tab.size());
     memcpy(st, tab.data(), sizeof(int32_t) * tab.size());
     LAIR_HIP(hipMemcpyAsync(T->tables.get(), st, sizeof(int32_t) * tab.size(),
                             hipMemcpyHostToDevice, s));
-    T->blob.alloc(std::max<size_t>(total, 256), s);
     a->blob = T->blob.get();
     for (int32_t l = 0; l + 1 < nl; ++l) {
         src[l].blob = T->blob.get();
@@ -1296,8 +1310,10 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     }
     // the systems' tails, one workgroup each
     if (lists && !h->batch_tail) {
-        h->batch_tail = mixed ? make_batch_tail<float>(h, runs, s)
-                              : make_batch_tail<double>(h, runs, s);
+        h->batch_tail = unless_no_memory([&] {
+            return mixed ? make_batch_tail<float>(h, runs, s)
+                         : make_batch_tail<double>(h, runs, s);
+        });
         if (!h->batch_tail) {
             h->batch_tail.reset(new Tail());      // none: past every level
             h->batch_tail->start = nlev;
