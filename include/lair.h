@@ -346,7 +346,7 @@ lair_status lair_solve_batch(lair_hierarchy *h, const double *b, double *x, doub
  * changes.  Synchronises `stream`.  Errors: EINVAL (NULL, or a zero or
  * non-finite diagonal entry; the hierarchy is left unchanged),
  * EUNSUPPORTED (block scaling on), ESINGULAR (the hierarchy is then unusable
- * until a successful update). */
+ * until a successful update: its cycles and solves return EINVAL). */
 lair_status lair_update_diag(lair_hierarchy *h, const double *diag, int32_t on_device,
                              void *stream);
 

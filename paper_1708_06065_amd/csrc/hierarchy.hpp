@@ -141,6 +141,7 @@ struct lair_hierarchy {
     // captured correction cycles, keyed by (precision, nrhs); replayed on a
     // private stream ordered against the caller's stream with events
     bool batch = false;                      // built by lair_setup_batch
+    bool usable = true;                      // false: a new diagonal failed halfway
     bool use_act = false;                    // cycles restricted to the active rows
     std::vector<uint8_t> active;             // systems still iterated
     // captured solve iterations (cycle + residual + norms), keyed by the

@@ -1453,6 +1453,18 @@ void update_diag_impl(lair_hierarchy *h, const double *diag, int32_t on_device,
         rb.run();
     }
     if (hb) fail(LAIR_EINVAL, "the new diagonal has a zero or non-finite entry");
+    // what a failed update leaves is not used again: no cycle runs, and so no
+    // tail or graph is made, until an update succeeds
+    h->usable = false;
+    struct Failed {
+        lair_hierarchy *h;
+        ~Failed() {
+            if (h->usable) return;
+            h->drop_graphs();
+            h->tails.clear();
+            h->batch_tail.reset();
+        }
+    } failed{h};
     LAIR_LAUNCH(k_set_diag, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, L0.A.rp.get(),
                 L0.A.cj.get(), L0.A.v.get(), dd);
     LAIR_LAUNCH_CHECK();
@@ -1463,17 +1475,6 @@ void update_diag_impl(lair_hierarchy *h, const double *diag, int32_t on_device,
     for (auto &t : h->tails) t.stale = true;
     if (h->batch_tail) h->batch_tail->stale = true;
     h->n_singular = 0;
-    // what a failed update leaves may not be used again
-    struct Failed {
-        lair_hierarchy *h;
-        bool done = false;
-        ~Failed() {
-            if (done) return;
-            h->drop_graphs();
-            h->tails.clear();
-            h->batch_tail.reset();
-        }
-    } failed{h};
     DevArr<int64_t> tmp;
     const int32_t prec = h->opt.precision == LAIR_FP64 ? LAIR_FP64 : LAIR_MIXED;
     for (size_t l = 0; l + 1 < h->L.size(); ++l) {
@@ -1508,7 +1509,7 @@ void update_diag_impl(lair_hierarchy *h, const double *diag, int32_t on_device,
     finish_cycle_operators(h, s);
     level_stats_and_cc(h);
     LAIR_HIP(hipStreamSynchronize(s));
-    failed.done = true;
+    h->usable = true;
 }
 
 // Union of a batch: the systems' matrices placed block-diagonally, rows of

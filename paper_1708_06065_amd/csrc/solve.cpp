@@ -741,7 +741,17 @@ static bool valid_nrhs(int32_t nrhs) {
     return nrhs == 1 || nrhs == 2 || nrhs == 4 || nrhs == 8 || nrhs == 16 || nrhs == 32;
 }
 
+// After a new diagonal that failed the levels hold values of both diagonals
+// and the coarsest grid may have neither an inverse nor factors (its pivots
+// are then whatever the memory held).
+static void check_usable(const lair_hierarchy *h) {
+    if (!h->usable)
+        fail(LAIR_EINVAL, "the last new diagonal failed: the hierarchy is unusable until an "
+             "update succeeds");
+}
+
 void check_nrhs(const lair_hierarchy *h, int32_t nrhs) {
+    check_usable(h);
     if (!valid_nrhs(nrhs)) fail(LAIR_EINVAL, "nrhs must be 1, 2, 4, 8, 16 or 32");
     if (h->nsys > 1 && nrhs != 1)
         fail(LAIR_EINVAL, "a hierarchy of a batch takes one right-hand side per system");
@@ -1223,6 +1233,7 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
     auto t0 = Clock::now();
     check_solve_args(h, b, x, rtol, maxit);
     if (!h->batch) fail(LAIR_EINVAL, "the hierarchy was not built by lair_setup_batch");
+    check_usable(h);
     ensure_vectors(h, 1, s);
     if (h->nsys == 1) ensure_tail(h, 1, h->opt.precision == LAIR_MIXED, false, s);
     Level &L0 = *h->L[0];
