@@ -405,7 +405,9 @@ lair_status lair_export(const lair_hierarchy *h, int32_t level, int32_t what,
  * local_lstsq, interp, spgemm_count, spgemm_fill, validate, coarse_setup,
  * residual, restrict, interpolate, jacobi, scatter, norm, coarse_solve,
  * cast, spgemm_compact, lump, tail (the small levels of a cycle in one
- * workgroup).  Process-wide; not for concurrent use from several host threads. */
+ * workgroup), graph (an iteration replayed from its HIP graph: alg_bytes and
+ * alg_flops 0).  Process-wide; not for concurrent use from several host
+ * threads. */
 lair_status lair_profile_begin(const char *categories);
 lair_status lair_profile_end(char *json, int64_t *len);
 

@@ -829,7 +829,12 @@ static void run_iteration(lair_hierarchy *h, int kind, int32_t nrhs, const void 
         g = &h->graphs.back();
     }
     if (g->exec) {
+        ProfScope ps("graph", s, 0.0);
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        const bool timed = prof_kernel_events(s, &e0, &e1);
+        if (timed) LAIR_HIP(hipEventRecord(e0, s));
         LAIR_HIP(hipGraphLaunch(g->exec, s));
+        if (timed) LAIR_HIP(hipEventRecord(e1, s));
         return;
     }
     body(s);
