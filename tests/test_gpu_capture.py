@@ -86,3 +86,44 @@ def test_transposes_on_a_captured_stream_are_refused(lair):
         got = h.cycle_transpose(g, torch.zeros_like(g))
     s.synchronize()
     assert torch.equal(got, want)
+
+
+# 40^2: every level in one workgroup; 97^2: launched levels above it.  A graph
+# recorded before the workgroup's operators are packed, or after a new
+# diagonal has made them old, holds launches for every level: the same bits
+@pytest.mark.parametrize("nrhs", [1, 4])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("m", [40, 97])
+def test_cycle_in_a_callers_graph(lair, m, precision, nrhs):
+    import torch
+    print("case: captured cycle", m, precision, nrhs, flush=True)
+    w = W.workload_c4(m)
+    args = (w["rowptr"], w["col"], w["val"])
+    rng = np.random.default_rng(m)
+    shape = (w["n"],) if nrhs == 1 else (w["n"], nrhs)
+    b, z = torch.zeros(shape, dtype=torch.float64, device="cuda"), torch.zeros(
+        shape, dtype=torch.float64, device="cuda")
+    h = lair.setup(*args, interp="direct", precision=precision)
+
+    def check(call):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            z.zero_()
+            call(b, z)
+        for _ in range(3):
+            b.copy_(torch.as_tensor(rng.standard_normal(shape), device="cuda"))
+            graph.replay()
+            torch.cuda.synchronize()
+            got = z.clone()
+            assert torch.equal(got, h.cycle(b, torch.zeros_like(b)))
+            assert torch.isfinite(got).all()
+
+    h.cycle_noalloc(b, z)             # the scratch array's address is known
+    torch.cuda.synchronize()
+    check(h.cycle_noalloc)            # recorded before anything is packed
+    check(h.cycle)                    # with the workgroup
+    check(h.cycle_noalloc)
+    h.update_diag(_diagonals(w, 1)[0])
+    check(h.cycle)                    # packed from the old diagonal
+    check(h.cycle)                    # and packed again
+    h.free()
