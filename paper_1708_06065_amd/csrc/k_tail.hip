@@ -62,15 +62,35 @@ __device__ __forceinline__ int share_pos(int lo, int g, int m, int lg, int ll) {
 }
 
 // ---------------------------------------------------------------------------
-// Packing: one wave per chunk, blockIdx.y the set.
+// Packing: one wave per chunk, the sets of all levels in one launch.  It is
+// part of a hierarchy's first cycle and of the first after a new diagonal, and
+// bound by latency: its launches (one a level before) and, in rows of some
+// hundred entries, one load after another (before: the diagonal looked for in
+// every entry, the entries copied one by one).  So the diagonal is found by
+// halves, and a lane fetches PACK_K entries at a time.  First cycle of a
+// 66 x 66 grid 133 -> 109 us (later ones 55), of a 1000-row arrow matrix
+// 495 -> 255, of 3000 rows with three of 500 entries 350 -> 190.
 // ---------------------------------------------------------------------------
 constexpr int PACK_BS = 256;
+constexpr int PACK_SETS = 32;       // the table is a kernel argument (4 KB)
+constexpr int PACK_K = 16;
+
+template <class VT>
+struct PackArgs {
+    char *blob;
+    int32_t nset;
+    int32_t block0[PACK_SETS + 1];  // each set's first block
+    TailSource<VT> src[PACK_SETS];
+};
 
 template <class VT>
 __global__ void __launch_bounds__(PACK_BS)
-k_tail_pack(const TailSources<VT> t) {
-    const TailSource<VT> &S = t.src[blockIdx.y];
-    const int ch = blockIdx.x * (PACK_BS / WAVE) + threadIdx.x / WAVE;
+k_tail_pack(const PackArgs<VT> t) {
+    static_assert(sizeof(PackArgs<VT>) <= 4096, "");
+    int set = 0;
+    for (int q = 1; q < t.nset; ++q) set += (int)blockIdx.x >= t.block0[q] ? 1 : 0;
+    const TailSource<VT> &S = t.src[set];
+    const int ch = ((int)blockIdx.x - t.block0[set]) * (PACK_BS / WAVE) + threadIdx.x / WAVE;
     if (ch >= S.nchunk) return;
     const int lane = threadIdx.x & (WAVE - 1);
     const int lg = S.lg, ll = S.ll, g = lane & ((1 << lg) - 1);
@@ -92,14 +112,17 @@ k_tail_pack(const TailSources<VT> t) {
         k -= S.chunk0[lo] << (6 - lg);
         hi_k = S.rows ? S.run[lo + 1] - S.run[lo] : (int)(S.rseg[lo + 1] - rb);
     }
+    const int32_t *cj = S.cj;
+    const VT *v = S.v;
     int i = 0, p0 = 0, p1 = 0;
     if (k < hi_k) {
         i = S.rows ? S.rows[base + k] : (int)(base + k);
         p0 = S.rp[i];
         p1 = S.rp[i + 1];
     }
-    int mine = 0;                          // entries of this lane's share
-    while (share_pos(p0, g, mine, lg, ll) < p1) ++mine;
+    // entries of this lane's share: whole steps, and its part of the last one
+    const int step = lg + ll, rest = (p1 - p0) & ((1 << step) - 1);
+    const int mine = (((p1 - p0) >> step) << ll) + min(max(rest - (g << ll), 0), 1 << ll);
     int ng = (mine + U - 1) / U;
 #pragma unroll
     for (int o = WAVE / 2; o > 0; o >>= 1) ng = max(ng, __shfl_xor(ng, o));
@@ -107,31 +130,54 @@ k_tail_pack(const TailSources<VT> t) {
     char *blob = t.blob;
     if (lane == 0) reinterpret_cast<uint16_t *>(blob + S.dst.o_used)[ch] = (uint16_t)ng;
     if (S.diag) {
-        VT d = (VT)0;
-        for (int p = p0; p < p1; ++p)
-            if (S.cj[p] == i) d = S.v[p];
+        const int p = bsearch_i32(cj + p0, p1 - p0, i);
         reinterpret_cast<uint16_t *>(blob + S.dst.o_row)[(size_t)ch * WAVE + lane] =
             k < hi_k ? (uint16_t)(i - rb) : (uint16_t)0;
-        reinterpret_cast<VT *>(blob + S.dst.o_diag)[(size_t)ch * WAVE + lane] = d;
+        reinterpret_cast<VT *>(blob + S.dst.o_diag)[(size_t)ch * WAVE + lane] =
+            p >= 0 ? v[p0 + p] : (VT)0;
     }
     uint16_t *col = reinterpret_cast<uint16_t *>(blob + S.dst.o_col);
     VT *val = reinterpret_cast<VT *>(blob + S.dst.o_val);
-    for (int m = 0; m < max(ng, 1) * U; ++m) {
-        const int p = share_pos(p0, g, m, lg, ll);
-        const size_t o = (((size_t)ch * smax + m / U) * WAVE + lane) * U + m % U;
-        col[o] = p < p1 ? (uint16_t)(S.cj[p] - c0) : (uint16_t)ncol;
-        val[o] = p < p1 ? S.v[p] : (VT)0;
+    const int entries = max(ng, 1) * U;
+    for (int m0 = 0; m0 < entries; m0 += PACK_K) {
+        int c[PACK_K];
+        VT a[PACK_K];
+#pragma unroll
+        for (int u = 0; u < PACK_K; ++u) {
+            const int p = share_pos(p0, g, m0 + u, lg, ll);
+            c[u] = p < p1 ? (int)(cj[p] - c0) : ncol;
+            a[u] = p < p1 ? v[p] : (VT)0;
+        }
+#pragma unroll
+        for (int u = 0; u < PACK_K; ++u) {
+            const int m = m0 + u;
+            if (m >= entries) break;
+            const size_t o = (((size_t)ch * smax + m / U) * WAVE + lane) * U + m % U;
+            col[o] = (uint16_t)c[u];
+            val[o] = a[u];
+        }
     }
 }
 
 template <class VT>
-void launch_tail_pack(const TailSources<VT> &t, hipStream_t s) {
-    int32_t most = 0;
-    for (const auto &S : t.src) most = std::max(most, S.nchunk);
-    if (most == 0) return;
-    LAIR_LAUNCH((k_tail_pack<VT>), dim3(blocks_for(most, PACK_BS / WAVE), TAIL_SETS),
-                dim3(PACK_BS), 0, s, t);
-    LAIR_LAUNCH_CHECK();
+void launch_tail_pack(const std::vector<TailSources<VT>> &levels, hipStream_t s) {
+    PackArgs<VT> t{};
+    auto flush = [&] {
+        if (t.nset == 0) return;
+        LAIR_LAUNCH((k_tail_pack<VT>), dim3((unsigned)t.block0[t.nset]), dim3(PACK_BS), 0, s, t);
+        LAIR_LAUNCH_CHECK();
+        t.nset = 0;
+    };
+    for (const auto &level : levels)
+        for (const auto &S : level.src) {
+            if (S.nchunk == 0) continue;
+            t.blob = level.blob;
+            t.src[t.nset] = S;
+            t.block0[t.nset + 1] =
+                t.block0[t.nset] + (int32_t)blocks_for(S.nchunk, PACK_BS / WAVE);
+            if (++t.nset == PACK_SETS) flush();
+        }
+    flush();
 }
 
 // ---------------------------------------------------------------------------
@@ -698,8 +744,8 @@ void max_rows(int m, const int32_t *const *rp, const int32_t *nrows, int32_t *ou
     rb.run();
 }
 
-template void launch_tail_pack<double>(const TailSources<double> &, hipStream_t);
-template void launch_tail_pack<float>(const TailSources<float> &, hipStream_t);
+template void launch_tail_pack<double>(const std::vector<TailSources<double>> &, hipStream_t);
+template void launch_tail_pack<float>(const std::vector<TailSources<float>> &, hipStream_t);
 template void launch_tail<double>(const TailArgs<double> &, int, const double *, double *,
                                   const double *, hipStream_t);
 template void launch_tail<float>(const TailArgs<float> &, int, const float *, float *,

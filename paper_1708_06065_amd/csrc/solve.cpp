@@ -254,7 +254,7 @@ static std::vector<TailSources<VT>> &tail_sources(Tail &t) {
 // Pack every level (again, when the operators have new values).
 template <class VT>
 static void pack_tail(Tail &t, hipStream_t s) {
-    for (auto &src : tail_sources<VT>(t)) launch_tail_pack<VT>(src, s);
+    launch_tail_pack<VT>(tail_sources<VT>(t), s);
     t.stale = false;
 }
 

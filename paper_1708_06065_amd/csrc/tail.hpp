@@ -6,6 +6,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 namespace lair {
 
@@ -98,9 +99,9 @@ int32_t tail_groups(int32_t max_row, int lg, int ll, bool u4);
 // place the parts of a set (smax and u4 given) of w-byte values from `at` on;
 // returns where the next set may begin
 size_t tail_layout(TailSet &t, size_t at, int32_t nchunk, bool rows, size_t w);
-// pack every set of a level (sets with nchunk = 0 are left out)
+// pack every set of the levels (sets with nchunk = 0 are left out)
 template <class VT>
-void launch_tail_pack(const TailSources<VT> &t, hipStream_t s);
+void launch_tail_pack(const std::vector<TailSources<VT>> &levels, hipStream_t s);
 template <class VT>
 void launch_tail(const TailArgs<VT> &a, int mode, const VT *b, VT *x, const VT *r,
                  hipStream_t s);
