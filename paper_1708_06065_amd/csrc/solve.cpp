@@ -423,13 +423,39 @@ static void ensure_tail(lair_hierarchy *h, int32_t nrhs, bool mixed, bool transp
     h->tails.push_back(std::move(T));
 }
 
+// Whether tails are worth their workgroups on a batch.  Up to one system a CU
+// (a workgroup's 1,024 threads take its registers) all of them take as long as
+// the largest; beyond, each level of a system costs a CU about 9.5 us.  A
+// launched level costs 21 us and the coarsest solve 8, and the rows 1 us per
+// 4,500.  Microseconds per iteration (30 iterations, m x m grids):
+//   levels   m     systems: tails / launches
+//     1     11      300:  58 /  67    1,000:  87 /  76
+//     2     13      500:  68 /  83    1,500: 133 / 103    2,000: 168 / 118
+//     3     16    1,000: 112 / 125    2,000: 212 / 171
+//     4     24    1,000: 171 / 200    2,000: 311 / 331
+//     6     40      128:  76 / 171    1,000: 276 / 421
+//     7     66      300: 251 / 408
+static bool batch_tail_pays(const lair_hierarchy *h, const Tail &T) {
+    int dev = 0, cus = 0;
+    LAIR_HIP(hipGetDevice(&dev));
+    LAIR_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    double levels = 0.0, rows = 0.0;
+    for (int32_t q = 0; q < h->nsys; ++q) {
+        const Level &Lv = *h->L[T.top[q]];
+        levels += h->sys_levels[q] - T.top[q];
+        rows += (double)(Lv.seg[q + 1] - Lv.seg[q]);
+    }
+    return 9.5 * levels / std::max(1, cus) <=
+           8.0 + 21.0 * (double)(h->L.size() - 1 - T.start) + rows / 4500.0;
+}
+
 // The tail of a batch solve: one workgroup per system, from the first level
 // at which the system is as small as a single system's tail may be (its
 // entries taken from the union's mean row).  Systems of a batch differ by a
 // factor of a hundred, so each has a start of its own; the levels above are
 // launched over the systems that still need them, and the tail is launched
 // where the last system's starts.  nullptr: no tail (a coarsest block without
-// an inverse, too many levels).
+// an inverse, too many levels, or systems for which it does not pay).
 template <class VT>
 static std::unique_ptr<Tail> make_batch_tail(lair_hierarchy *h,
                                              const std::vector<std::array<std::vector<int32_t>, 3>> &runs,
@@ -471,6 +497,7 @@ static std::unique_ptr<Tail> make_batch_tail(lair_hierarchy *h,
         depth = std::max(depth, t);
     }
     T->start = (size_t)depth;
+    if (!batch_tail_pays(h, *T)) return nullptr;
     auto &a = tail_args<VT>(*T);
     a.reset(new TailArgs<VT>());
     a->nlv = nl;
