@@ -1287,7 +1287,6 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
                                 sizeof(int32_t) * (4 * h->L.size() + 1 + 5 * maxseg), s);
         for (size_t l = 0; l < h->L.size(); ++l) {
             Level &Lv = *h->L[l];
-            Lv.act_cnt = reinterpret_cast<int32_t *>(h->act_upload.get()) + 4 * l;
             Lv.act_rows.alloc((size_t)std::max(Lv.n, 1), s);
             if (l + 1 < h->L.size()) {
                 Lv.act_p.alloc((size_t)std::max(Lv.n, 1), s);
@@ -1295,6 +1294,9 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
                 Lv.act_c.alloc((size_t)std::max(Lv.nrc >= 0 ? Lv.nrc : Lv.nc, 1), s);
             }
         }
+        // (what says that all of them are there, after an allocation failed too)
+        for (size_t l = 0; l < h->L.size(); ++l)
+            h->L[l]->act_cnt = reinterpret_cast<int32_t *>(h->act_upload.get()) + 4 * l;
         moved = true;
     }
     if (h->ss_nblk == 0) {
@@ -1309,7 +1311,6 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
             }
             bstart.push_back((int64_t)bsys.size());
         }
-        h->ss_nblk = (int32_t)bsys.size();
         h->ss_sys.alloc(bsys.size(), s);
         h->ss_lo.alloc(blo.size(), s);
         h->ss_start.alloc(bstart.size(), s);
@@ -1321,6 +1322,7 @@ lair_status solve_batch_impl(lair_hierarchy *h, const double *b, double *x,
         LAIR_HIP(hipMemcpyAsync(h->ss_start.get(), bstart.data(),
                                 sizeof(int64_t) * bstart.size(), hipMemcpyHostToDevice, s));
         LAIR_HIP(hipStreamSynchronize(s));     // pageable sources
+        h->ss_nblk = (int32_t)bsys.size();
         moved = true;
     }
     if (moved) h->drop_graphs();
