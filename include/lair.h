@@ -237,7 +237,13 @@ lair_status lair_setup(const lair_csr *A, const lair_cf_levels *cf,
 
 /* One V-cycle on device vectors: x <- x + B (b - A x), nrhs interleaved
  * right-hand sides (nrhs in 1, 2, 4, 8, 16, 32).  With block scaling, b is
- * the unscaled right-hand side.  Asynchronous on `stream`. */
+ * the unscaled right-hand side.  Asynchronous on `stream`.
+ * The first cycle of a hierarchy (for each nrhs), and the first after a new
+ * diagonal, packs the operators of its small levels, unless there is no
+ * memory for them or the stream is captured: they are then launched level by
+ * level, with the same results.  A graph that a caller captures around a
+ * cycle or a transposed cycle holds the operators' values of that time in
+ * part: capture it again after lair_update_diag. */
 lair_status lair_cycle(lair_hierarchy *h, const double *b, double *x,
                        int32_t nrhs, void *stream);
 
@@ -298,7 +304,9 @@ lair_status lair_solve_transpose(lair_hierarchy *h, const double *g,
                                  int32_t maxit, lair_info *info,
                                  void *stream);
 
-/* One transposed cycle (the adjoint of lair_cycle). */
+/* One transposed cycle (the adjoint of lair_cycle).  EDEVICE when its
+ * operators have to be made (after a new diagonal) and the stream that they
+ * are made on, that of the last setup or update, is itself captured. */
 lair_status lair_cycle_transpose(lair_hierarchy *h, const double *g,
                                  double *lam, int32_t nrhs, void *stream);
 
@@ -343,7 +351,8 @@ lair_status lair_solve_batch(lair_hierarchy *h, const double *b, double *x, doub
  * while the local solves (Eq. (system)), the interpolation weights, the
  * Galerkin products (Sec. 2.1) and the coarsest factors are recomputed.
  * For a family A(c) = A0 + diag(c) this replaces a full setup when only c
- * changes.  Synchronises `stream`.  Errors: EINVAL (NULL, or a zero or
+ * changes.  Graphs that the caller captured around cycles of the hierarchy
+ * must be captured again.  Synchronises `stream`.  Errors: EINVAL (NULL, or a zero or
  * non-finite diagonal entry; the hierarchy is left unchanged),
  * EUNSUPPORTED (block scaling on), ESINGULAR (the hierarchy is then unusable
  * until a successful update: its cycles and solves return EINVAL). */

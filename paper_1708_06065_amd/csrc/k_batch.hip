@@ -214,29 +214,6 @@ void launch_active_lists(int32_t nlists, int32_t nruns, const int32_t *ptr, cons
     LAIR_LAUNCH_CHECK();
 }
 
-// Per-system sum of squares (one block per system, fixed order).
-__global__ void __launch_bounds__(256)
-k_seg_sumsq(const int64_t *seg, const uint8_t *active, const double *r, double *out) {
-    __shared__ double sh[256];
-    int32_t s = blockIdx.x;
-    if (active && !active[s]) return;      // a finished system keeps its last norm
-    double acc = 0.0;
-    for (int64_t i = seg[s] + threadIdx.x; i < seg[s + 1]; i += 256) acc += r[i] * r[i];
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[s] = sh[0];
-}
-
-void launch_seg_sumsq(int32_t nsys, const int64_t *seg, const double *r, double *out,
-                      hipStream_t s, const uint8_t *active) {
-    LAIR_LAUNCH(k_seg_sumsq, dim3(nsys), dim3(256), 0, s, seg, active, r, out);
-    LAIR_LAUNCH_CHECK();
-}
-
 // Per-system sums of squares over several blocks per system: block b sums
 // rows [blo[b], min(blo[b] + SEG_CHUNK, end of its system)) into part[b];
 // then one block per system adds its blocks' partials in order.

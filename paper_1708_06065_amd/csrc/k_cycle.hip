@@ -857,19 +857,6 @@ void op_fill(VT *x, VT val, int64_t n, hipStream_t s) {
     LAIR_LAUNCH_CHECK();
 }
 
-template <class VT>
-__global__ void k_copy(const VT *x, VT *y, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = x[i];
-}
-
-template <class VT>
-void op_copy(const VT *x, VT *y, int64_t n, hipStream_t s) {
-    if (n == 0) return;
-    LAIR_LAUNCH((k_copy<VT>), dim3(blocks_for(n, 256)), dim3(256), 0, s, x, y, n);
-    LAIR_LAUNCH_CHECK();
-}
-
 // The same expressions as the sweep kernels, whose product with a zero iterate
 // is zero: one launch where a fill, a sweep and a scatter were three.
 __global__ void __launch_bounds__(256)
@@ -1317,8 +1304,6 @@ template void op_scatter<double>(const int32_t *, int32_t, const double *, doubl
 template void op_scatter<float>(const int32_t *, int32_t, const float *, float *, int32_t, hipStream_t, int32_t);
 template void op_fill<double>(double *, double, int64_t, hipStream_t);
 template void op_fill<float>(float *, float, int64_t, hipStream_t);
-template void op_copy<double>(const double *, double *, int64_t, hipStream_t);
-template void op_copy<float>(const float *, float *, int64_t, hipStream_t);
 template void op_dense_solve<double>(int32_t, const double *, const int32_t *, const double *, double *, int32_t, bool, hipStream_t);
 template void op_dense_solve<float>(int32_t, const double *, const int32_t *, const float *, float *, int32_t, bool, hipStream_t);
 

@@ -21,10 +21,6 @@ constexpr int KRY_GS_MAX = 24;   // basis vectors a thread holds in k_gs
 // partial[(blk * kstride + kbase + k) * R + q] = the block's part of
 // sum_i V_{kbase+k}[i R + q] w[i R + q], k < kc <= KRY_KC.  The grid stride
 // is a multiple of R, so each thread keeps one right-hand side.
-struct KryScale {
-    double v[32];
-};
-
 __global__ void __launch_bounds__(KRY_BS)
 k_mdot(int64_t m, int R, const double *V, int64_t ldv, int kbase, int kc, int kstride,
        const double *w, double *partial) {
@@ -138,6 +134,10 @@ k_maxpy(int64_t m, int R, const double *V, int64_t ldv, int kc, const double *co
 }
 
 // out[i R + q] = w[i R + q] * s[q], the factors a kernel argument
+struct KryScale {
+    double v[32];
+};
+
 __global__ void __launch_bounds__(KRY_BS)
 k_scale_rhs(int64_t m, int R, const double *w, const KryScale s, double *out) {
     __shared__ double sc[32];
@@ -180,8 +180,8 @@ void op_gram_schmidt(int64_t n, int32_t R, const double *V, int64_t ldv, int32_t
     if (!pow2_rhs(R)) fail(LAIR_EINVAL, "right-hand sides must be a power of two up to 32");
     if (kc < 1 || n == 0) return;
     const int64_t m = n * R;
-    // a thread holds its entry of every basis vector; longer bases, and 32
-    // right-hand sides of long ones, take the separate kernels
+    // a thread holds its entry of every basis vector; longer bases take the
+    // separate kernels
     if (kc > KRY_GS_MAX) {
         op_maxpy(n, R, V, ldv, kc, coef, w, s);
         if (dots) op_mdot(n, R, V, ldv, kc, w, partial, out, s);

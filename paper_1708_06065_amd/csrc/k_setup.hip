@@ -359,11 +359,6 @@ int64_t scan_counts_i32(const int32_t *cnt, int32_t *out, int64_t n,
     return scan_impl(CountsF{cnt}, out, n, s, tmp, max_out, flag, flag_out);
 }
 
-int64_t scan_counts_i64(const int32_t *cnt, int64_t *out, int64_t n, hipStream_t s,
-                        DevArr<int64_t> &tmp, int64_t *max_out) {
-    return scan_impl(CountsF{cnt}, out, n, s, tmp, max_out, nullptr, nullptr);
-}
-
 int64_t scan_flags_i8(const int8_t *flags, int8_t want, int32_t *out, int64_t n,
                       hipStream_t s, DevArr<int64_t> &tmp) {
     return scan_impl(FlagsF{flags, want}, out, n, s, tmp, nullptr, nullptr, nullptr);

@@ -214,8 +214,6 @@ inline int team_for_mean(double mean_len) {
 // exclusive scan of f(i) for i < n into out[0..n], returns out[n]
 // optionally also returns the largest count and copies a device flag back
 // in the same synchronisation
-int64_t scan_counts_i64(const int32_t *cnt, int64_t *out, int64_t n, hipStream_t s,
-                        DevArr<int64_t> &tmp, int64_t *max_out = nullptr);
 int64_t scan_counts_i32(const int32_t *cnt, int32_t *out, int64_t n,
                         hipStream_t s, DevArr<int64_t> &tmp,
                         int64_t *max_out = nullptr, const int32_t *flag = nullptr,
@@ -455,8 +453,6 @@ void op_scatter(const int32_t *rows, int32_t nrows, const VT *t, VT *x,
                 int32_t nrhs, hipStream_t s, int32_t row0 = 0);
 template <class VT>
 void op_fill(VT *x, VT val, int64_t n, hipStream_t s);
-template <class VT>
-void op_copy(const VT *x, VT *y, int64_t n, hipStream_t s);
 // The first sweep of a transposed cycle, on the C rows (kind[i] = 1) of a
 // zero iterate: x_i = y_i = omega g_i / d_i there and 0 elsewhere.
 void op_first_sweep(int64_t n, int32_t nrhs, const int8_t *kind, const double *g,
@@ -558,8 +554,6 @@ void launch_stopped_rows(int32_t nsys, const int64_t *seg, const uint8_t *stoppe
 int32_t relax_list(int32_t nsys, const int64_t *seg, const uint8_t *stopped,
                    const int32_t *clist, int32_t nc, DevArr<int32_t> &out,
                    hipStream_t s, DevArr<int64_t> &tmp);
-void launch_seg_sumsq(int32_t nsys, const int64_t *seg, const double *r, double *out,
-                      hipStream_t s, const uint8_t *active = nullptr);
 int64_t seg_sum_chunk();
 void launch_seg_sumsq_blocks(int32_t nsys, int32_t nblk, const int32_t *bsys,
                              const int64_t *blo, const int64_t *bstart, const int64_t *seg,

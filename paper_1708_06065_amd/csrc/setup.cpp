@@ -1496,14 +1496,13 @@ void update_diag_impl(lair_hierarchy *h, const double *diag, int32_t on_device,
         }
         DevCSR AP, K;
         spgemm(Lv.A, Lv.max_row, Lv.P, AP, s, tmp);
-        int32_t mr = spgemm(Lv.R, Lv.st.s_max + 1, AP, K, s, tmp, h->L[l + 1]->A.nnz);
+        spgemm(Lv.R, Lv.st.s_max + 1, AP, K, s, tmp, h->L[l + 1]->A.nnz);
         Level &Nx = *h->L[l + 1];
         if (K.nnz != Nx.A.nnz)
             fail(LAIR_EDEVICE, "coarse operator pattern changed on update (level %zu)", l + 1);
         if (K.nnz > 0)
             LAIR_HIP(hipMemcpyAsync(Nx.A.v.get(), K.v.get(), sizeof(double) * (size_t)K.nnz,
                                     hipMemcpyDeviceToDevice, s));
-        (void)mr;
     }
     finish_coarsest(h);
     finish_cycle_operators(h, s);
