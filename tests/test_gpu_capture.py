@@ -1,6 +1,9 @@
 """GPU: cycles recorded into a caller's own graph.  The graph is replayed
 several times with eager calls and synchronizations between, and every replay
 is compared with the eager call bit for bit."""
+import contextlib
+import gc
+
 import numpy as np
 import pytest
 
@@ -16,6 +19,20 @@ def lair():
     assert torch.cuda.is_available()
     lair.load_library()
     return lair
+
+
+@contextlib.contextmanager
+def _recording(torch, graph, **kw):
+    """Record into graph with the garbage collector off: hierarchies and graphs
+    that earlier tests left in reference cycles wait for the device when they
+    are collected, which must not happen inside a capture."""
+    gc.collect()
+    gc.disable()
+    try:
+        with torch.cuda.graph(graph, **kw):
+            yield
+    finally:
+        gc.enable()
 
 
 def _diagonals(w, k):
@@ -45,7 +62,7 @@ def test_transposed_cycle_captured_after_a_new_diagonal(lair, m):
     torch.cuda.synchronize()
     lam = torch.zeros_like(g)
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):
+    with _recording(torch, graph):
         lam.zero_()
         h.cycle_transpose(g, lam)
     assert torch.equal(h.cycle_transpose(g, torch.zeros_like(g)), want)
@@ -77,11 +94,12 @@ def test_transposes_on_a_captured_stream_are_refused(lair):
     s.synchronize()
     lam = torch.zeros_like(g)
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph, stream=s):
+    with _recording(torch, graph, stream=s):
         lam.zero_()
         with pytest.raises(lair.LairError) as e:
             h.cycle_transpose(g, lam)
     assert e.value.status == -3
+    del e                    # its traceback holds this frame, and so the graph
     with torch.cuda.stream(s):
         got = h.cycle_transpose(g, torch.zeros_like(g))
     s.synchronize()
@@ -107,7 +125,7 @@ def test_cycle_in_a_callers_graph(lair, m, precision, nrhs):
 
     def check(call):
         graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph):
+        with _recording(torch, graph):
             z.zero_()
             call(b, z)
         for _ in range(3):
