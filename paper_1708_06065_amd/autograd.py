@@ -50,6 +50,7 @@ class LairSolve(torch.autograd.Function):
         diag = val[pos].contiguous()
         if reuse is not None and reuse.get("h") is not None:
             h = reuse["h"]
+            reuse["current"] = None          # nobody's, should the update fail
             h.update_diag(diag)
         else:
             h = _setup(rowptr, col, val, **opts)

@@ -59,3 +59,23 @@ def test_failed_update(lair, nsys, precision):
     for _ in range(30):
         x.zero_()
         assert torch.equal(solve(h, x)[0], want)
+
+
+def test_gradient_after_a_failed_forward(lair):
+    """A forward pass whose new diagonal fails on a kept hierarchy: the
+    backward pass of the forward before it puts its own diagonal back."""
+    import torch
+    from paper_1708_06065_amd.autograd import LairSolve
+    rp, cj, _ = (torch.as_tensor(a, device="cuda") for a in ONES)
+    val0 = torch.ones(16, dtype=torch.float64, device="cuda")
+    b = torch.as_tensor(np.random.default_rng(7).standard_normal(4), device="cuda")
+    opts = dict(reuse={})
+    LairSolve.apply(b, torch.full_like(b, 2.0), rp, cj, val0, opts)
+    c = torch.full_like(b, 3.0).requires_grad_()
+    x = LairSolve.apply(b, c, rp, cj, val0, opts)
+    with pytest.raises(lair.LairError):
+        LairSolve.apply(b, torch.zeros_like(b), rp, cj, val0, opts)
+    x.sum().backward()
+    A = np.ones((4, 4)) + 3.0 * np.eye(4)
+    want = -np.linalg.solve(A.T, np.ones(4)) * np.linalg.solve(A, b.cpu().numpy())
+    assert np.allclose(c.grad.cpu().numpy(), want, rtol=1e-9, atol=0)
