@@ -68,7 +68,7 @@ __device__ __forceinline__ int share_pos(int lo, int g, int m, int lg, int ll) {
 // hundred entries, one load after another (before: the diagonal looked for in
 // every entry, the entries copied one by one).  So the diagonal is found by
 // halves, and a lane fetches PACK_K entries at a time.  First cycle of a
-// 66 x 66 grid 133 -> 109 us (later ones 55), of a 1000-row arrow matrix
+// 66 x 66 grid 133 -> 109 us, of a 1000-row arrow matrix
 // 495 -> 255, of 3000 rows with three of 500 entries 350 -> 190.
 // ---------------------------------------------------------------------------
 constexpr int PACK_BS = 256;
